@@ -50,7 +50,8 @@ __global__ void __launch_bounds__(256) clear_u32(uint32_t *__restrict__ p, int n
 }
 
 // ---- pack A, int16: one workgroup per padded row ---------------------------
-// Writes Ah/Al[i][0, k_pad) and corrA[i] = 32768*sum(h) + 128*sum(l) mod 2^32,
+// Writes row i of the packed A (2 k_pad bytes: per 64 elements their 64 high
+// limbs, then their 64 offset low limbs) and corrA[i] = 32768*sum(h) + 128*sum(l) mod 2^32,
 // and, if corrB is given, zeroes corrB[0, n_pad).
 // For the int16-output update (bsA given): also the exact per-block limb
 // sums of the row, block b = [b bspan, (b + 1) bspan) of the planes (bspan a
@@ -60,7 +61,7 @@ __global__ void __launch_bounds__(256) clear_u32(uint32_t *__restrict__ p, int n
 template <bool VEC>
 __global__ void __launch_bounds__(256)
 pack_a_i16(const int16_t *__restrict__ A, int64_t lda, int m, int k, int k_pad,
-           int8_t *__restrict__ Ah, int8_t *__restrict__ Al, uint32_t *__restrict__ corrA,
+           int8_t *__restrict__ Apk, uint32_t *__restrict__ corrA,
            uint32_t *__restrict__ corrB, int n_pad, uint32_t *__restrict__ bsA, int bspan,
            int nblocks, uint32_t *__restrict__ clr, int nclr) {
     const int i = blockIdx.x, tid = threadIdx.x;
@@ -76,8 +77,7 @@ pack_a_i16(const int16_t *__restrict__ A, int64_t lda, int m, int k, int k_pad,
     }
     const int len = i < m ? k : 0;
     const int16_t *arow = A + (int64_t)(i < m ? i : 0) * lda;
-    int8_t *hrow = Ah + (int64_t)i * k_pad;
-    int8_t *lrow = Al + (int64_t)i * k_pad;
+    int8_t *prow = Apk + (int64_t)i * k_pad * 2;
     int sh = 0, sl = 0;
     for (int e0 = tid * 8; e0 < k_pad; e0 += 256 * 8) {
         const v4i raw = load16<2, VEC>(arow, e0, len);
@@ -103,8 +103,9 @@ pack_a_i16(const int16_t *__restrict__ A, int64_t lda, int m, int k, int k_pad,
                 atomicAdd(&bsum[e0 / bspan][1], bl);
             }
         }
-        *(uint2 *)(hrow + e0) = make_uint2(h0, h1);
-        *(uint2 *)(lrow + e0) = make_uint2(l0, l1);
+        int8_t *dst = prow + 2 * e0 - (e0 & 63);
+        *(uint2 *)dst = make_uint2(h0, h1);
+        *(uint2 *)(dst + 64) = make_uint2(l0, l1);
     }
     if (bsA != nullptr) {
         __syncthreads();
@@ -136,7 +137,7 @@ pack_a_i16(const int16_t *__restrict__ A, int64_t lda, int m, int k, int k_pad,
 template <bool VEC>
 __global__ void __launch_bounds__(256)
 pack_a_i16_rows(const int16_t *__restrict__ A, int64_t lda, int m, int k, int k_pad,
-                int8_t *__restrict__ Ah, int8_t *__restrict__ Al, uint32_t *__restrict__ corrA,
+                int8_t *__restrict__ Apk, uint32_t *__restrict__ corrA,
                 uint32_t *__restrict__ corrB, int n_pad, uint32_t *__restrict__ bsA, int bspan,
                 int m_pad, uint32_t *__restrict__ clr, int nclr) {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -158,8 +159,9 @@ pack_a_i16_rows(const int16_t *__restrict__ A, int64_t lda, int m, int k, int k_
         h1 = perm(y3, y2, 0x07050301u) & m1;
         l0 = (perm(y1, y0, 0x06040200u) ^ 0x80808080u) & m0;
         l1 = (perm(y3, y2, 0x06040200u) ^ 0x80808080u) & m1;
-        *(uint2 *)(Ah + (int64_t)i * k_pad + e0) = make_uint2(h0, h1);
-        *(uint2 *)(Al + (int64_t)i * k_pad + e0) = make_uint2(l0, l1);
+        int8_t *dst = Apk + (int64_t)i * k_pad * 2 + 2 * e0 - (e0 & 63);
+        *(uint2 *)dst = make_uint2(h0, h1);
+        *(uint2 *)(dst + 64) = make_uint2(l0, l1);
     }
     // half-wave sums (32 lanes, 256 elements), then the row's
     int sh = sum4(h1, sum4(h0, 0)), sl = sum4(l1, sum4(l0, 0));
@@ -213,8 +215,7 @@ pack_a_i8(const int8_t *__restrict__ A, int64_t lda, int m, int k, int k_pad,
 template <int ES, bool VEC>
 __global__ void __launch_bounds__(256)
 pack_b(const void *__restrict__ Bv, int64_t ldb, int k, int n, int k_pad, int kspan, int n_pad,
-       int8_t *__restrict__ Bp0, int8_t *__restrict__ Bp1, uint32_t *__restrict__ corrB,
-       uint32_t *__restrict__ bsB = nullptr, int bspan = 0) {
+       int8_t *__restrict__ Bpk, uint32_t *__restrict__ corrB, uint32_t *__restrict__ bsB = nullptr, int bspan = 0) {
     constexpr int P = ES;                 // output planes
     constexpr int CC = ES == 2 ? 8 : 4;   // 16-byte column chunks per workgroup (64 columns)
     constexpr int RG = 256 / CC;          // row groups of 4 rows
@@ -307,15 +308,21 @@ pack_b(const void *__restrict__ Bv, int64_t ldb, int k, int n, int k_pad, int ks
         // P planes x 64 columns x ROWS bytes, in 16-byte chunks.
         constexpr int CH = ROWS / 16;
         for (int idx = tid; idx < P * 64 * CH; idx += 256) {
-            const int plane = idx / (64 * CH), rem = idx % (64 * CH);
-            const int col = rem / CH, ch = rem % CH;
+            // (int16: consecutive threads write the two planes of 64 rows, 128
+            // contiguous bytes)
+            const int col = idx / (P * CH), rem = idx % (P * CH);
+            const int plane = P == 2 ? (rem >> 2) & 1 : 0;
+            const int ch = P == 2 ? (rem >> 3) * 4 + (rem & 3) : rem;
             const u32 *src = &T[plane][col][4 * ch];
             v4i v;
             v.x = (int)src[0];
             v.y = (int)src[1];
             v.z = (int)src[2];
             v.w = (int)src[3];
-            int8_t *dst = (plane ? Bp1 : Bp0) + (int64_t)(j0 + col) * k_pad + p0 + ch * 16;
+            // int16: per 64 rows of B their high limbs, then their low limbs
+            const int e = p0 + ch * 16;
+            int8_t *dst = Bpk + (int64_t)(j0 + col) * k_pad * P +
+                          (P == 2 ? 2 * e - (e & 63) + 64 * plane : e);
             *(v4i *)dst = v;
         }
         __syncthreads();
@@ -330,8 +337,9 @@ pack_b(const void *__restrict__ Bv, int64_t ldb, int k, int n, int k_pad, int ks
 }
 
 // ---- the packed-operand GEMM ---------------------------------------------
-// A planes: P x m_pad x k_pad (row stride lda_p, plane stride a_plane), B
-// planes: P x n_pad x k_pad; ktiles k-tiles of 64 from the given origin. NST is
+// A: m_pad rows of row stride lda_p, B: n_pad rows (its columns) of row stride
+// ldb_p, both in packed form, RB = 64 ES bytes of a row per k-tile of 64 (int16:
+// 64 high limbs, then 64 offset low limbs); ktiles k-tiles of 64 from the given origin. NST is
 // the number of LDS stages of the DMA ring (4, or 3 for tiles whose stage
 // is too large for four).
 // EPI 1 (int16 only): C is int16 (passed through the int32 pointer) and
@@ -358,8 +366,8 @@ pack_b(const void *__restrict__ Bv, int64_t ldb, int k, int n, int k_pad, int ks
 template <int ES, int BM, int BN, int WM, int WN, int NST, int EPI = 0, bool RAGGED = false,
           bool SKIPZ = false>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64, 1)
-igemm_packed(const int8_t *__restrict__ Ap, int64_t lda_p, int64_t a_plane,
-             const int8_t *__restrict__ Bp, int64_t ldb_p, int64_t b_plane,
+igemm_packed(const int8_t *__restrict__ Ap, int64_t lda_p,
+             const int8_t *__restrict__ Bp, int64_t ldb_p,
              const uint32_t *__restrict__ corrA, const uint32_t *__restrict__ corrB,
              uint32_t kconst, int32_t *__restrict__ C, int64_t ldc,
              int m, int n, int ktiles, int tiles_m, int tiles_n, int epi, int kcb = 0,
@@ -376,12 +384,18 @@ igemm_packed(const int8_t *__restrict__ Ap, int64_t lda_p, int64_t a_plane,
     constexpr int NW = (BM / WM) * WGN;
     static_assert(NW == 4 || NW == 8, "four or eight waves per workgroup");
     static_assert(NST == 3 || NST == 4, "three or four LDS stages");
-    constexpr int APL = BM * 64, BPL = BN * 64;
-    constexpr int STAGE = P * (APL + BPL);
+    // A row of a k-tile is RB bytes, in LDS as in memory: with int16 one whole
+    // 128-byte line per request. (A compute unit keeps a bounded number of
+    // line requests in flight, and rows of 64 bytes, one per limb plane, took
+    // twice as many.)
+    constexpr int RB = 64 * P;
+    constexpr int APL = BM * RB, BPL = BN * RB;
+    constexpr int STAGE = APL + BPL;
     static_assert(NST * STAGE <= 160 * 1024, "gfx950 LDS");
-    // 1 KB DMA blocks per stage: NBA hold the A planes, NBB the B planes;
-    // each wave moves DPA of the A blocks and DPB of the B blocks.
-    constexpr int NBA = P * BM / 16, NBB = P * BN / 16;
+    // 1 KB DMA blocks per stage: NBA hold the A rows, NBB the B rows; each
+    // wave moves DPA of the A blocks and DPB of the B blocks.
+    constexpr int RPB = 1024 / RB;  // rows per block
+    constexpr int NBA = BM / RPB, NBB = BN / RPB;
     static_assert(NBA % NW == 0 && NBB % NW == 0, "DMA blocks per wave");
     constexpr int DPA = NBA / NW, DPB = NBB / NW, DPW = DPA + DPB;
     static_assert(DPW <= 15, "outstanding DMA count fits s_waitcnt");
@@ -445,64 +459,71 @@ igemm_packed(const int8_t *__restrict__ Ap, int64_t lda_p, int64_t a_plane,
     }
 
     // DMA: lane i of a 1 KB block writes LDS bytes [16i, 16i+16), i.e. row
-    // r0 + i/4 of the block, physical chunk i%4, which holds logical chunk
-    // (i%4) ^ swz(row); r0 is a multiple of 16, so swz(row) = swz(i/4). The
-    // source is a wave-uniform block base plus a per-lane 32-bit offset that
-    // is the same for every block of an operand (the planner keeps 16 rows
-    // of a plane below 2^32 bytes).
-    const u32 lrow = (u32)(lane >> 2);
-    const u32 lq = (u32)((lane & 3) ^ swz(lane >> 2));
-    const u32 a_loff = lrow * (u32)lda_p + 16u * lq;
-    const u32 b_loff = lrow * (u32)ldb_p + 16u * lq;
+    // r0 + i / CPR of the block, physical chunk i % CPR, which holds the
+    // logical chunk (i % CPR) ^ rswz(row). The source is a wave-uniform block
+    // base plus a per-lane 32-bit offset that is the same for every block of
+    // an operand whose r0 has the same place in the swizzle's period of 16
+    // rows: all of them (int8, 16 rows per block), or the even and the odd
+    // ones (int16, 8 rows; the odd ones' chunks differ in bit 2). The planner
+    // keeps 16 rows of a plane below 2^32 bytes.
+    constexpr int CPR = RB / 16;
+    auto rswz = [](int row) -> int { return P == 2 ? (row >> 1) & 7 : swz(row); };
+    const u32 lrow = (u32)(lane / CPR);
+    const u32 lq = (u32)((lane % CPR) ^ rswz(lane / CPR));
+    static_assert(P == 1 || (DPA % 2 == 0 && DPB % 2 == 0), "even and odd blocks by d");
+    const u32 a_loff[2] = {lrow * (u32)lda_p + 16u * lq,
+                           lrow * (u32)lda_p + 16u * (P == 2 ? lq ^ 4u : lq)};
+    const u32 b_loff[2] = {lrow * (u32)ldb_p + 16u * lq,
+                           lrow * (u32)ldb_p + 16u * (P == 2 ? lq ^ 4u : lq)};
     const int8_t *src[DPW];
     int ldsoff[DPW];
 #pragma unroll
     for (int d = 0; d < DPW; ++d) {
         if (d < DPA) {
             const int b = wave * DPA + d;
-            const int plane = b / (BM / 16), r0 = (b % (BM / 16)) * 16;
-            src[d] = Ap + plane * a_plane + (int64_t)(m0 + r0) * lda_p;
+            src[d] = Ap + (int64_t)(m0 + b * RPB) * lda_p;
             ldsoff[d] = b * 1024;
         } else {
-            const int bb = wave * DPB + (d - DPA);
-            const int plane = bb / (BN / 16), r0 = (bb % (BN / 16)) * 16;
-            src[d] = Bp + plane * b_plane + (int64_t)(n0 + r0) * ldb_p;
-            ldsoff[d] = (NBA + bb) * 1024;
+            const int b = wave * DPB + (d - DPA);
+            src[d] = Bp + (int64_t)(n0 + b * RPB) * ldb_p;
+            ldsoff[d] = (NBA + b) * 1024;
         }
     }
     // DMA blocks [D0, D1) of k-tile kt into stage s.
     auto dma_range = [&](auto s, int kt, auto d0, auto d1) {
         constexpr int D0 = decltype(d0)::value, D1 = decltype(d1)::value;
         char *dst = stage(s);
-        const int64_t koff = (int64_t)kt * 64;
+        const int64_t koff = (int64_t)kt * RB;
 #pragma unroll
         for (int d = D0; d < D1; ++d)
-            dma16(src[d] + koff + (d < DPA ? a_loff : b_loff), (lds_void *)(dst + ldsoff[d]));
+            dma16(src[d] + koff + (d < DPA ? a_loff[d & 1] : b_loff[(d - DPA) & 1]),
+                  (lds_void *)(dst + ldsoff[d]));
     };
 
-    // Fragment reads (same LDS layout as the fused kernels).
+    // Fragment reads: logical chunk 4 plane + (chunk of the 64 k) of a row.
     const int fr = M::frag_row(lane);
-    int a_rbase[2], b_rbase[2];
+    int a_rbase[2][P], b_rbase[2][P];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-        const int cq = (M::frag_chunk(lane, ks) ^ swz(fr)) << 4;
-        a_rbase[ks] = (wm0 + fr) * 64 + cq;
-        b_rbase[ks] = (wn0 + fr) * 64 + cq;
-    }
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const int cq = ((4 * p + M::frag_chunk(lane, ks)) ^ rswz(fr)) << 4;
+            a_rbase[ks][p] = (wm0 + fr) * RB + cq;
+            b_rbase[ks][p] = APL + (wn0 + fr) * RB + cq;
+        }
     v4i fa[2][P][TM], fb[2][P][TN];
     auto read_frags = [&](auto slot, auto s, auto ks) {
         constexpr int SL = decltype(slot)::value;
         constexpr int KS = decltype(ks)::value;
-        const char *As = stage(s);
-        const char *Bs = As + P * APL;
+        const char *st = stage(s);
 #pragma unroll
         for (int p = 0; p < P; ++p) {
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                fb[SL][p][j] = *(const v4i *)(Bs + p * BPL + b_rbase[KS] + j * MF * 64);
+                fb[SL][p][j] = *(const v4i *)(st + b_rbase[KS][p] + j * MF * RB);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
-                fa[SL][p][i] = *(const v4i *)(As + p * APL + a_rbase[KS] + i * MF * 64);
+                fa[SL][p][i] = *(const v4i *)(st + a_rbase[KS][p] + i * MF * RB);
         }
     };
 
@@ -951,10 +972,8 @@ int launch_pack_a(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k, 
     uint32_t *corrB = b_part_to_clear != nullptr
                           ? (uint32_t *)((int8_t *)b_part_to_clear + L.off_corr_b)
                           : nullptr;
-    const int64_t a_plane = L.m_pad * L.k_pad;
     const dim3 g((unsigned)L.m_pad);
     if (es == 2) {
-        int8_t *Al = Apk + a_plane;
         const int16_t *A16 = (const int16_t *)A;
         // int16-output update: A's block sums, and B's cleared for pack_b
         const int bspan = sums != nullptr ? (int)(nblocks == 1 ? L.k_pad : kc) : 0;
@@ -966,17 +985,17 @@ int launch_pack_a(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k, 
             // short rows: one wave per row (m_pad is a multiple of 128)
             const dim3 g4((unsigned)(L.m_pad / 4));
             if (va)
-                pack_a_i16_rows<true><<<g4, 256, 0, stream>>>(A16, lda, mi, ki, kp, Apk, Al, corrA,
+                pack_a_i16_rows<true><<<g4, 256, 0, stream>>>(A16, lda, mi, ki, kp, Apk, corrA,
                                                               corrB, np, sums, bspan, mp, clr, nclr);
             else
-                pack_a_i16_rows<false><<<g4, 256, 0, stream>>>(A16, lda, mi, ki, kp, Apk, Al,
+                pack_a_i16_rows<false><<<g4, 256, 0, stream>>>(A16, lda, mi, ki, kp, Apk,
                                                                corrA, corrB, np, sums, bspan, mp,
                                                                clr, nclr);
         } else if (va)
-            pack_a_i16<true><<<g, 256, 0, stream>>>(A16, lda, mi, ki, kp, Apk, Al, corrA, corrB, np,
+            pack_a_i16<true><<<g, 256, 0, stream>>>(A16, lda, mi, ki, kp, Apk, corrA, corrB, np,
                                                     sums, bspan, nb, clr, nclr);
         else
-            pack_a_i16<false><<<g, 256, 0, stream>>>(A16, lda, mi, ki, kp, Apk, Al, corrA, corrB,
+            pack_a_i16<false><<<g, 256, 0, stream>>>(A16, lda, mi, ki, kp, Apk, corrA, corrB,
                                                      np, sums, bspan, nb, clr, nclr);
     } else {
         const int8_t *A8 = (const int8_t *)A;
@@ -999,7 +1018,6 @@ int launch_pack_b(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k, 
     const int ni = (int)n, ki = (int)k, kp = (int)L.k_pad, np = (int)L.n_pad;
     int8_t *Bpk = wb + L.off_b;
     uint32_t *corrB = (uint32_t *)(wb + L.off_corr_b);
-    const int64_t b_plane = L.n_pad * L.k_pad;
     if (es == 2 && clear_corr) {
         clear_u32<<<dim3((unsigned)((np + 255) / 256)), 256, 0, stream>>>(corrB, np);
         if (hipGetLastError() != hipSuccess) return IGEMM_EHIP;
@@ -1007,21 +1025,20 @@ int launch_pack_b(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k, 
     const dim3 g((unsigned)(L.n_pad / 64), (unsigned)L.b_slices);
     const int ks = (int)L.kspan;
     if (es == 2) {
-        int8_t *Bl = Bpk + b_plane;
         // int16-output update: B's block sums (after A's; cleared by pack_a_i16)
         uint32_t *sb = sums != nullptr ? sums + 2 * nblocks * L.m_pad : nullptr;
         const int bspan = sums != nullptr ? (int)(nblocks == 1 ? L.k_pad : kc) : 0;
         if (vb)
-            pack_b<2, true><<<g, 256, 0, stream>>>(B, ldb, ki, ni, kp, ks, np, Bpk, Bl, corrB, sb,
+            pack_b<2, true><<<g, 256, 0, stream>>>(B, ldb, ki, ni, kp, ks, np, Bpk, corrB, sb,
                                                    bspan);
         else
-            pack_b<2, false><<<g, 256, 0, stream>>>(B, ldb, ki, ni, kp, ks, np, Bpk, Bl, corrB, sb,
+            pack_b<2, false><<<g, 256, 0, stream>>>(B, ldb, ki, ni, kp, ks, np, Bpk, corrB, sb,
                                                     bspan);
     } else {
         if (vb)
-            pack_b<1, true><<<g, 256, 0, stream>>>(B, ldb, ki, ni, kp, ks, np, Bpk, Bpk, corrB);
+            pack_b<1, true><<<g, 256, 0, stream>>>(B, ldb, ki, ni, kp, ks, np, Bpk, corrB);
         else
-            pack_b<1, false><<<g, 256, 0, stream>>>(B, ldb, ki, ni, kp, ks, np, Bpk, Bpk, corrB);
+            pack_b<1, false><<<g, 256, 0, stream>>>(B, ldb, ki, ni, kp, ks, np, Bpk, corrB);
     }
     return hipGetLastError() == hipSuccess ? IGEMM_OK : IGEMM_EHIP;
 }
@@ -1043,7 +1060,7 @@ int launch_srs_packed(const igemm_plan &p, int64_t m, int64_t n, int64_t k, int6
     if (nblocks < 1 || nblocks > 64 || (nblocks > 1 && kc % 256 != 0)) return IGEMM_EINVAL;
     const int8_t *wa = (const int8_t *)a_part, *wb = (const int8_t *)b_part;
     const int8_t *Apk = wa + L.off_a, *Bpk = wb + L.off_b;
-    const int64_t a_plane = L.m_pad * L.k_pad, b_plane = L.n_pad * L.k_pad;
+    const int64_t ld = 2 * L.k_pad;  // bytes of a packed row
     const int kb = nblocks == 1 ? (int)L.k_pad : (int)kc;  // block span in the planes
     // the block sums, written by the pack kernels
     uint32_t *sa = sums, *sb = sums + 2 * nblocks * L.m_pad;
@@ -1065,8 +1082,8 @@ int launch_srs_packed(const igemm_plan &p, int64_t m, int64_t n, int64_t k, int6
         const uint32_t kcon = 16384u * (uint32_t)kc;
 #define IGEMM_SRS_MULTI(E)                                                                 \
     igemm_packed<2, 128, 128, 64, 32, 4, E><<<grid, 512, 0, stream>>>(                    \
-        Apk, L.k_pad, a_plane, Bpk, L.k_pad, b_plane, sa, sb, kcon, (int32_t *)C, ldc, mi, \
-        ni, ktl, tm, tn, epi, kcb, (int)L.m_pad, (int)L.n_pad)
+        Apk, ld, Bpk, ld, sa, sb, kcon, (int32_t *)C, ldc, mi, ni, ktl,                   \
+        tm, tn, epi, kcb, (int)L.m_pad, (int)L.n_pad)
         if (shift == 0 && kc == 256)
             IGEMM_SRS_MULTI(5);
         else if (shift == 0)
@@ -1093,17 +1110,17 @@ int launch_srs_packed(const igemm_plan &p, int64_t m, int64_t n, int64_t k, int6
         if (span <= 512) {
             // short blocks: eight waves, the zero tiles' MFMAs skipped
             igemm_packed<2, 128, 128, 64, 32, 4, 1, false, true><<<grid, 512, 0, stream>>>(
-                Apk + k0, L.k_pad, a_plane, Bpk + k0, L.k_pad, b_plane, sa + 2 * q * L.m_pad,
+                Apk + 2 * k0, ld, Bpk + 2 * k0, ld, sa + 2 * q * L.m_pad,
                 sb + 2 * q * L.n_pad, 16384u * (uint32_t)real, (int32_t *)C, ldc, mi, ni,
                 (int)(span / 64), tm, tn, epi, (int)((real + 63) / 64));
         } else if (ktiles % 4 == 0)
             igemm_packed<2, 128, 128, 64, 64, 4, 1><<<grid, 256, 0, stream>>>(
-                Apk + k0, L.k_pad, a_plane, Bpk + k0, L.k_pad, b_plane, sa + 2 * q * L.m_pad,
+                Apk + 2 * k0, ld, Bpk + 2 * k0, ld, sa + 2 * q * L.m_pad,
                 sb + 2 * q * L.n_pad, 16384u * (uint32_t)real, (int32_t *)C, ldc, mi, ni, ktiles,
                 tm, tn, epi);
         else
             igemm_packed<2, 128, 128, 64, 64, 4, 1, true><<<grid, 256, 0, stream>>>(
-                Apk + k0, L.k_pad, a_plane, Bpk + k0, L.k_pad, b_plane, sa + 2 * q * L.m_pad,
+                Apk + 2 * k0, ld, Bpk + 2 * k0, ld, sa + 2 * q * L.m_pad,
                 sb + 2 * q * L.n_pad, 16384u * (uint32_t)real, (int32_t *)C, ldc, mi, ni, ktiles,
                 tm, tn, epi);
         if (hipGetLastError() != hipSuccess) return IGEMM_EHIP;
@@ -1122,11 +1139,10 @@ int launch_multiply(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k
     const int8_t *Bpk = wb + L.off_b;
     const uint32_t *corrA = (const uint32_t *)(wa + L.off_corr_a);
     const uint32_t *corrB = (const uint32_t *)(wb + L.off_corr_b);
-    const int64_t a_plane = L.m_pad * L.k_pad, b_plane = L.n_pad * L.k_pad;
     const KernelDesc &d = kKernels[p.kernel];
     const int tm = (int)(L.m_pad / d.bm), tn = (int)(L.n_pad / d.bn);
     const int8_t *Asrc = L.pack_a ? wa + L.off_a : (const int8_t *)A;
-    const int64_t lda_p = L.pack_a ? L.k_pad : lda;
+    const int64_t ldb_p = es * L.k_pad, lda_p = L.pack_a ? ldb_p : lda;  // bytes of a row
     const dim3 grid((unsigned)p.grid);
     if (es == 2 && L.k_pad <= 512) {
         // Short k (one chunk of four or eight k-tiles): eight waves of 64 x 32,
@@ -1135,8 +1151,8 @@ int launch_multiply(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k
         // 256 58.9 / 61.9, 290 68.3 / 71.5, 512 75.0 / 77.8.
         const int kr = (int)((k + kBK - 1) / kBK);
         igemm_packed<2, 128, 128, 64, 32, 4, 0, false, true><<<grid, 512, 0, stream>>>(
-            Asrc, lda_p, a_plane, Bpk, L.k_pad, b_plane, corrA, corrB, 16384u * (uint32_t)k, C,
-            ldc, mi, ni, (int)(L.k_pad / kBK), tm, tn, 0, kr);
+            Asrc, lda_p, Bpk, ldb_p, corrA, corrB, 16384u * (uint32_t)k, C, ldc, mi, ni,
+            (int)(L.k_pad / kBK), tm, tn, 0, kr);
         return hipGetLastError() == hipSuccess ? IGEMM_OK : IGEMM_EHIP;
     }
     // One launch per k chunk; the row and column corrections and the
@@ -1159,15 +1175,13 @@ int launch_multiply(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k
         const uint32_t kc16 = first ? 16384u * (uint32_t)k : 0u;
         if (es == 2 && ragged)
             igemm_packed<2, 128, 128, 64, 64, 4, 0, true><<<grid, 256, 0, stream>>>(
-                Asrc + k0, lda_p, a_plane, Bpk + k0, L.k_pad, b_plane, cA, corrB, kc16, C, ldc,
-                mi, ni, ktiles, tm, tn, 0);
+                Asrc + 2 * k0, lda_p, Bpk + 2 * k0, ldb_p, cA, corrB, kc16, C, ldc, mi, ni, ktiles, tm, tn, 0);
         else if (es == 2)
             igemm_packed<2, 128, 128, 64, 64, 4><<<grid, 256, 0, stream>>>(
-                Asrc + k0, lda_p, a_plane, Bpk + k0, L.k_pad, b_plane, cA, corrB, kc16, C, ldc,
-                mi, ni, ktiles, tm, tn, 0);
+                Asrc + 2 * k0, lda_p, Bpk + 2 * k0, ldb_p, cA, corrB, kc16, C, ldc, mi, ni, ktiles, tm, tn, 0);
         else
             igemm_packed<1, 256, 256, 64, 128, 4><<<grid, 512, 0, stream>>>(
-                Asrc + k0, lda_p, 0, Bpk + k0, L.k_pad, 0, nullptr, nullptr, 0u, C, ldc, mi, ni,
+                Asrc + k0, lda_p, Bpk + k0, ldb_p, nullptr, nullptr, 0u, C, ldc, mi, ni,
                 ktiles, tm, tn, 0);
         if (hipGetLastError() != hipSuccess) return IGEMM_EHIP;
     }
