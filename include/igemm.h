@@ -107,6 +107,8 @@ int igemm_i8(int64_t m, int64_t n, int64_t k,
  *            the rows of A and B are whole 16-byte chunks; up to 4, 8, 16
  *            or 32 (16 at most for more than 16 rows) when B's rows are
  *            whole 8-byte chunks; and to 4 otherwise.
+ *            The ring kernels' automatic slices are whole k-tiles (128 int8,
+ *            64 int16); a given count is kept, in units of 64.
  * Semantics, memory and errors are those of igemm_i16 / igemm_i8.
  */
 int igemm_i16_ex(int64_t m, int64_t n, int64_t k,
@@ -133,7 +135,8 @@ typedef struct igemm_plan {
     int64_t tiles;     /* C tiles = ceil(m/bm) * ceil(n/bn)                */
     int64_t grid;      /* workgroups launched = tiles * split              */
     int threads;       /* threads per workgroup                            */
-    int vec_a, vec_b;  /* 1 if A / B rows take 16-byte vector loads      */
+    int vec_a, vec_b;  /* 1 if A / B rows take 16-byte vector loads (ring  */
+                       /* kernels: both 1 if staged by DMA)               */
     int limb_products; /* int8 MFMA products per operand pair: 4 or 1      */
     int packed;        /* 1 if operands are packed into a workspace first  */
     int64_t workspace_bytes; /* device workspace the call needs (0: none)  */

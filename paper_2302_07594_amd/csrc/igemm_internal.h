@@ -35,6 +35,10 @@ enum KernelId {
     K_I8_DIRECT_256x256,
     K_I16_SMALL_64x64,
     K_I16_STREAM,
+    K_I8_RING_128x128,
+    K_I8_RING_64x128,
+    K_I16_RING_128x128,
+    K_I16_RING_64x64,
     K_COUNT
 };
 
@@ -141,6 +145,12 @@ bool small_ok(int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, const
 bool small_rg_ok(int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, const void *B,
                  int64_t ldb, int64_t ldc);
 
+// The ring kernel's staging (igemm_ring.h): by DMA, for operands whose rows
+// start at 4-byte addresses (convolutions: channel rows of whole 16-byte
+// chunks) and whose windows take 32-bit offsets (plan vec_a = vec_b = 1), or
+// through registers, any alignment (0).
+bool is_ring(int id);
+
 // Kernel launches for a validated plan (stream is a hipStream_t). The packed
 // launch needs a workspace of at least plan.workspace_bytes, 256-byte aligned.
 // The streaming kernel for few-row int8 products.
@@ -200,6 +210,17 @@ int launch_pack_b(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k, 
 int launch_direct(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k, const void *A,
                   int64_t lda, const void *B, int64_t ldb, int32_t *C, int64_t ldc,
                   void *stream);
+// The ring kernel: one launch, k slices of plan.k_chunk (atomic adds). g:
+// the convolution's geometry, or null for a row-major A. The int16-output
+// form (srs) takes one block of k and no slices.
+int launch_ring(const igemm_plan &p, int64_t m, int64_t n, int64_t k, const void *A, int64_t lda,
+                const void *B, int64_t ldb, int32_t *C, int64_t ldc, const ConvGeom *g,
+                void *stream);
+int launch_ring_srs(const igemm_plan &p, int64_t m, int64_t n, int64_t k, const void *A,
+                    int64_t lda, const void *B, int64_t ldb, int16_t *C, int64_t ldc, int shift,
+                    int round_half_up, void *stream);
+const void *ring_i8(int id, bool conv, bool reg, int epi);
+const void *ring_i16(int id, bool conv, int epi);
 // The small-output int16 kernel: one launch, k slices of plan.k_chunk; and
 // its convolution variants (A gathered from X: gather 1, whole 64-channel
 // taps by DMA; gather 3, input runs through registers).

@@ -31,6 +31,10 @@ const KernelDesc kKernels[K_COUNT] = {
     {"i8_direct_256x256", 1, 256, 256, 64, 128, false},
     {"i16_small_64x64", 2, 64, 64, 32, 32, false},
     {"i16_stream_32x64", 2, 32, 64, 16, 16, false},
+    {"i8_ring_128x128", 1, 128, 128, 64, 64, false},
+    {"i8_ring_64x128", 1, 64, 128, 32, 64, false},
+    {"i16_ring_128x128", 2, 128, 128, 64, 32, false},
+    {"i16_ring_64x64", 2, 64, 64, 32, 32, false},
 };
 
 // Largest grid (in workgroups) of one launch: the dispatch packet counts
@@ -349,6 +353,99 @@ static bool small_pays(int64_t m, int64_t n, int64_t k, int num_cu) {
     return tiles * cdiv(cdiv(k, kBK), kSmallKtMax) <= 2 * (int64_t)num_cu;
 }
 
+bool is_ring(int id) {
+    return id == K_I8_RING_128x128 || id == K_I8_RING_64x128 || id == K_I16_RING_128x128 ||
+           id == K_I16_RING_64x64;
+}
+
+// Modelled time (us, without the launch) of a ring kernel with s k slices,
+// fitted to its measured times on 256 compute units: `r` workgroups per unit
+// share it, each k-tile (128 int8, 64 int16) costs the unit a fixed part and
+// one per workgroup, and slices pay for their atomic adds into C, about 2.4 us
+// per million. Measured (us, s = 1 / 2 / 4): int8 64 x 128 tiles 64 x 4096 x
+// 4096 21.1 / 14.0 / 9.6, 256 x 4096 x 4096 21.1 / 16.2 / 20.2, 1024^3 6.5 /
+// 8.7 / 13.1; int16 64 x 64 tiles 64 x 4096 x 4096 39.1 / 23.0 / 15.2, 1024^3
+// 11.3 / 11.7 / 16.7, 128 x 128 tiles 512 x 4096 x 4096 55.0 / 43.3 / 54.4.
+// Tile shapes: int8 2048 x 4096 x 4096 50.0 with 128 x 128 against 64.5 with
+// 64 x 128, 1536^3 17.0 against 13.9; int16 1024 x 4096 x 4096 74.8 with 128 x
+// 128 against 94.3 with 64 x 64, 1024^3 16.4 against 11.3.
+static double ring_time(int id, int64_t m, int64_t n, int64_t k, int64_t s, int num_cu) {
+    const KernelDesc &d = kKernels[id];
+    const int64_t kt = cdiv(cdiv(k, 128 / d.es), s);
+    const double r = (double)cdiv(tiles_of(id, m, n) * s, num_cu);
+    double t = 0;
+    switch (id) {
+        case K_I8_RING_128x128: t = 2.0 + (0.4 + 0.5 * r) * kt; break;
+        case K_I8_RING_64x128: t = 0.47 * r * kt; break;
+        case K_I16_RING_128x128: t = 2.0 + 0.95 * r * kt; break;
+        default: t = (0.22 + 0.28 * r) * kt; break;  // K_I16_RING_64x64
+    }
+    return t + (s > 1 ? 2.4e-6 * (double)m * (double)n * (double)s : 0.0);
+}
+
+// The slice count with the least modelled time.
+static int64_t ring_split(int id, int64_t m, int64_t n, int64_t k, int num_cu) {
+    const int64_t ktiles = cdiv(k, 128 / kKernels[id].es);
+    int64_t best = 1;
+    for (int64_t s = 2; s <= 16 && s <= ktiles; ++s)
+        if (ring_time(id, m, n, k, s, num_cu) < ring_time(id, m, n, k, best, num_cu)) best = s;
+    return best;
+}
+
+// The ring kernel (tile shape) with the least modelled time; sliced: k slices
+// are allowed.
+static int ring_kernel(int es, int64_t m, int64_t n, int64_t k, int num_cu, bool sliced) {
+    const int big = es == 2 ? K_I16_RING_128x128 : K_I8_RING_128x128;
+    const int small = es == 2 ? K_I16_RING_64x64 : K_I8_RING_64x128;
+    const int64_t sb = sliced ? ring_split(big, m, n, k, num_cu) : 1;
+    const int64_t ss = sliced ? ring_split(small, m, n, k, num_cu) : 1;
+    return ring_time(big, m, n, k, sb, num_cu) < ring_time(small, m, n, k, ss, num_cu) ? big
+                                                                                       : small;
+}
+
+// The ring kernel's plan: any alignment and any size whose windows take its
+// 32-bit offsets (bm rows of A and of C, one k-tile of B). k slices are whole
+// k-tiles (128 int8, 64 int16) unless the caller gave their number.
+static int ring_plan(int id, int es, int64_t m, int64_t n, int64_t k, const void *A, int64_t lda,
+                     const void *B, int64_t ldb, int64_t ldc, int num_cu, int split, bool conv,
+                     igemm_plan *out) {
+    const KernelDesc &d = kKernels[id];
+    const int64_t lim = (int64_t)0x7fff0000, bk = 128 / es;
+    int64_t a_win, b_row, c_win;
+    if (!mul_ok(d.bm * es, lda, &a_win) || !mul_ok(es, ldb, &b_row) ||
+        !mul_ok(d.bm * 4, ldc, &c_win) || (!conv && a_win + (k + bk) * es >= lim) ||
+        b_row >= lim / (bk + 1) - 16 || c_win >= lim)
+        return IGEMM_ENOTSUP;
+    const int64_t tiles = cdiv(m, d.bm) * cdiv(n, d.bn);
+    // (an explicit slice count is honoured in units of 64)
+    const int64_t unit = split > 0 ? kBK : bk, units = cdiv(k, unit);
+    int64_t s = split > 0 ? split : ring_split(id, m, n, k, num_cu);
+    if (s < cdiv(k, kMaxKChunk)) s = cdiv(k, kMaxKChunk);
+    if (s > units) s = units;
+    out->k_chunk = cdiv(units, s) * unit;
+    s = cdiv(k, out->k_chunk);
+    int64_t grid;
+    if (!mul_ok(tiles, s, &grid) || grid > kMaxGrid) return IGEMM_ENOTSUP;
+    // int8 by DMA: rows at 4-byte addresses, the k range's rows of B in one
+    // window.
+    const uintptr_t a = (uintptr_t)A, b = (uintptr_t)B;
+    const bool dma = es == 1 && a % 4 == 0 && b % 4 == 0 && (conv || lda % 4 == 0) &&
+                     ldb % 4 == 0 && b_row < lim / (out->k_chunk + bk) - 16;
+    out->kernel = id;
+    out->elem_bytes = es;
+    out->limb_products = es == 2 ? 4 : 1;
+    out->bm = d.bm;
+    out->bn = d.bn;
+    out->bk = (int)bk;
+    out->threads = (d.bm / d.wm) * (d.bn / d.wn) * 64;
+    out->split = (int)s;
+    out->tiles = tiles;
+    out->grid = grid;
+    out->vec_a = dma ? 1 : 0;
+    out->vec_b = dma ? 1 : 0;
+    return IGEMM_OK;
+}
+
 static int auto_kernel(int es, int64_t m, int64_t n, int64_t k, const void *A, int64_t lda,
                        const void *B, int64_t ldb, int64_t ldc, int num_cu, bool allow_packed) {
     const int pid = es == 2 ? K_I16_PACKED_128x128 : K_I8_PACKED_256x256;
@@ -374,6 +471,23 @@ static int auto_kernel(int es, int64_t m, int64_t n, int64_t k, const void *A, i
     if (es == 2 && !large && small_pays(m, n, k, num_cu) &&
         (small_ok(m, n, k, A, lda, B, ldb, ldc) || small_rg_ok(m, n, k, A, lda, B, ldb, ldc)))
         return K_I16_SMALL_64x64;
+    // The ring kernel takes what is left above the few-row shapes. int8: by DMA
+    // (rows at 4-byte addresses) anything over 32 rows (64^3 3.0 us against 9.0
+    // on 128x128 tiles, 512 x 4096 x 4096 22.9 against 34.7, 2048 x 4096 x 4096
+    // 50.0 against 89.3); through registers from 32 tiles (777 x 1111 x 2049
+    // 16.2 against 23.2; below, its bounds-checked last k-tile costs more than
+    // it gains: 146 x 501 x 801 9.5 against 7.3). int16: more than one k-tile
+    // and 32 tiles, or fewer over a long k (1536^3 25.9 against 45.8 us, 201 x
+    // 201 x 6001 10.3 against 17.9, 146 x 97 x 792 5.9 against 5.1).
+    igemm_plan rp{};
+    if (m > 32) {
+        const int rid = ring_kernel(es, m, n, k, num_cu, true);
+        if (ring_plan(rid, es, m, n, k, A, lda, B, ldb, ldc, num_cu, -1, false, &rp) == IGEMM_OK) {
+            const int64_t t = tiles_of(es == 2 ? K_I16_RING_64x64 : K_I8_RING_64x128, m, n);
+            if (es == 1 ? (rp.vec_a != 0 || t >= 32) : (k > kBK && (t >= 32 || k >= 2048)))
+                return rid;
+        }
+    }
     if (es == 1) {
         StreamShape ss;
         if (m <= 32 && n >= 512 && k >= 256 && (uintptr_t)B % 8 == 0 && ldb % 8 == 0 &&
@@ -509,6 +623,8 @@ int make_plan(int es, int64_t m, int64_t n, int64_t k, const void *A, int64_t ld
         out->packed_b_bytes = L.b_bytes;
         return IGEMM_OK;
     }
+    if (is_ring(id))
+        return ring_plan(id, es, m, n, k, A, lda, B, ldb, ldc, num_cu, split, false, out);
     if (id == K_I16_STREAM) {
         if (!i16_stream_ok(n, k, A, lda, B, ldb)) return IGEMM_EINVAL;
         return i16_stream_plan(m, n, k, lda, ldb, split, out);

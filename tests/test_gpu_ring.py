@@ -1,0 +1,108 @@
+"""GPU parity of the ring kernel (mid-size products) against the CPU oracle, bit for bit: edges of its tiles and
+k-tiles, every row alignment (DMA and register staging), k slices that end
+inside a k-tile, and the shapes
+where the automatic plans take it."""
+import numpy as np
+import pytest
+
+import workloads
+from gpu_util import describe_mismatch, gpu_gemm, oracle_gemm
+
+RING = {"i8": ("i8_ring_128x128", "i8_ring_64x128"),
+        "i16": ("i16_ring_128x128", "i16_ring_64x64")}
+
+
+def _ig():
+    import paper_2302_07594_amd as ig
+    return ig
+
+
+def _kid(name):
+    ig = _ig()
+    return [ig.igemm_kernel_name(i) for i in range(ig.igemm_num_kernels())].index(name)
+
+
+def _check(dt, m, n, k, name, split=-1, pad=(0, 0, 0), offsets=(0, 0, 0), seed=1):
+    A, B, C = workloads.random_operands(dt, m, n, k, seed=seed, lda=k + pad[0], ldb=n + pad[1],
+                                        ldc=n + pad[2])
+    _, got = gpu_gemm(A, B, C, m, n, k, kernel=_kid(name), split=split, offsets=offsets)
+    want = oracle_gemm(A, B, C, m, n, k)
+    assert np.array_equal(got, want), describe_mismatch(got, want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["i8", "i16"])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 5, 7), (64, 128, 128), (65, 129, 129),
+                                   (127, 255, 127), (130, 140, 16), (200, 15, 300),
+                                   (129, 260, 1000)], ids=lambda s: "x".join(map(str, s)))
+def test_ring_edges(dt, shape):
+    """One below, at and above the tiles and the k-tiles; rows and columns
+    shorter than the 16 bytes of one load; one to four k slices."""
+    for name in RING[dt]:
+        for split in (1, 2, 4):
+            _check(dt, *shape, name, split=split, seed=sum(shape))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["i8", "i16"])
+@pytest.mark.parametrize("off", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("pad", [0, 1, 2, 4])
+def test_ring_alignments(dt, off, pad):
+    """Every address of A and B modulo the dword and leading dimensions that
+    are and are not whole dwords: DMA where both allow it, registers else."""
+    for name in RING[dt]:
+        _check(dt, 140, 200, 332, name, split=2, pad=(pad, pad, 3), offsets=(off, off, 1),
+               seed=7 * off + pad)
+        _check(dt, 140, 200, 332, name, split=1, pad=(4, pad, 0), offsets=(0, off, 0), seed=5)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["i8", "i16"])
+def test_ring_extreme_values(dt):
+    """The types' ends over a k range of the launch limit and beyond it
+    (slices), where every partial sum is as large as it can be."""
+    info = np.iinfo(np.int8 if dt == "i8" else np.int16)
+    for k in (32768, 33000):
+        for a, b in ((info.min, info.min), (info.min, info.max), (info.max, info.max)):
+            A = np.full((40, k), a, dtype=info.dtype)
+            B = np.full((k, 72), b, dtype=info.dtype)
+            C = np.full((40, 72), -5, dtype=np.int32)
+            want = oracle_gemm(A, B, C, 40, 72, k)
+            for name in RING[dt]:
+                _, got = gpu_gemm(A, B, C, 40, 72, k, kernel=_kid(name))
+                assert np.array_equal(got, want), (name, k, a, b)
+
+
+def test_ring_plan_rules():
+    """Where the automatic plans take the ring kernel and how they slice it
+    (256 units, aligned buffers), and its 32-bit window limits."""
+    ig = _ig()
+
+    def plan(es, m, n, k, **kw):
+        p = ig.igemm_query_plan(es, m, n, k, num_cu=256, **kw)
+        return p["kernel_name"], p["split"], p["vec_a"]
+    assert plan(1, 512, 4096, 4096) == ("i8_ring_64x128", 1, 1)
+    assert plan(1, 64, 4096, 4096) == ("i8_ring_64x128", 4, 1)
+    assert plan(1, 2048, 4096, 4096) == ("i8_ring_128x128", 1, 1)
+    assert plan(1, 1000, 3001, 1777)[0].startswith("i8_ring") and \
+        plan(1, 1000, 3001, 1777)[2] == 0
+    assert plan(1, 64, 64, 64) == ("i8_ring_64x128", 1, 1)
+    assert not plan(1, 146, 501, 801)[0].startswith("i8_ring")    # few tiles, odd rows
+    assert not plan(1, 32, 300, 300)[0].startswith("i8_ring")     # few rows
+    assert plan(2, 1536, 1536, 1536)[0] == "i16_ring_128x128"
+    assert plan(2, 777, 1111, 2049)[0].startswith("i16_ring")
+    assert plan(2, 201, 201, 6001)[0] == "i16_ring_64x64"
+    assert not plan(2, 2000, 3000, 64)[0].startswith("i16_ring")  # one k-tile
+    # one k slice per 32768 at least; an explicit count in units of 64
+    assert plan(1, 512, 4096, 40000)[1] >= 2
+    p = ig.igemm_query_plan(1, 64, 64, 640, split=10)
+    assert p["split"] == 10 and p["k_chunk"] == 64
+    # a k range of B beyond 2 GiB is staged through registers; rows of A or C
+    # beyond it are refused
+    kid = _kid("i8_ring_128x128")
+    big = 1 << 20
+    assert ig.igemm_query_plan(1, 256, 256, 8192, ldb=big, kernel=kid, split=1)["vec_a"] == 0
+    for kw in ({"lda": 1 << 25}, {"ldb": 1 << 25}, {"ldc": 1 << 23}):
+        with pytest.raises(ig.IgemmError) as e:
+            ig.igemm_query_plan(1, 256, 256, 8192, kernel=kid, **kw)
+        assert e.value.status == ig.IGEMM_ENOTSUP
