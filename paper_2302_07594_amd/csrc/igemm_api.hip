@@ -276,8 +276,20 @@ int run_srs(int es, int64_t m, int64_t n, int64_t k, const void *A, int64_t lda,
         st = srs_packed_plan(es, m, n, k, A, lda, B, ldb, ldc, kc, num_cu_of_current_device(),
                              kernel, can_pack, &pp, &need);
         if (st != IGEMM_OK) return st;
-        if (pp.packed) {
-            if (workspace_bytes < need) return IGEMM_ENOMEM;
+        if (pp.packed && workspace_bytes < need) return IGEMM_ENOMEM;
+        // One block of short k, or at most one packed tile per compute unit:
+        // the ring kernel on the operands in place (the loop below) instead of
+        // the two pack passes and the packed multiply (us, ring / packed: m = n
+        // = 4096 with k = 290 47 / 63, 1024 85 / 103, 2048 145 / 163, 4096 267
+        // / 262; 2048 x 2048 x 4096 73 / 84).
+        igemm_plan rp;
+        const bool in_place =
+            pp.packed && kernel < 0 && nblocks == 1 &&
+            (k <= 2048 || pp.tiles <= num_cu_of_current_device()) &&
+            make_srs_plan(es, m, n, k, A, lda, B, ldb, ldc, num_cu_of_current_device(), -1,
+                          &rp) == IGEMM_OK &&
+            is_ring(rp.kernel);
+        if (pp.packed && !in_place) {
             // the pack kernels also take the per-block limb sums
             char *wb = (char *)workspace + pp.packed_a_bytes;
             uint32_t *sums = (uint32_t *)((char *)workspace + pp.workspace_bytes);

@@ -80,6 +80,8 @@ int launch_srs(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k, con
                int round_half_up, void *stream) {
     (void)es;
     if (p.split != 1) return IGEMM_EINVAL;
+    if (is_ring(p.kernel))
+        return launch_ring_srs(p, m, n, k, A, lda, B, ldb, C, ldc, shift, round_half_up, stream);
     const void *fn = fused_srs(p.kernel, p.vec_a != 0, p.vec_b != 0);
     if (fn == nullptr) return IGEMM_EINVAL;
     int mi = (int)m, ni = (int)n, ki = (int)k, kc = (int)p.k_chunk;

@@ -1,12 +1,14 @@
-"""GPU parity of the ring kernel (mid-size products) against the CPU oracle, bit for bit: edges of its tiles and
+"""GPU parity of the ring kernel (mid-size products and the int16-output
+update) against the CPU oracle, bit for bit: edges of its tiles and
 k-tiles, every row alignment (DMA and register staging), k slices that end
-inside a k-tile, and the shapes
+inside a k-tile, the conversion at shifts around its two forms, and the shapes
 where the automatic plans take it."""
 import numpy as np
 import pytest
 
 import workloads
 from gpu_util import describe_mismatch, gpu_gemm, oracle_gemm
+from test_gpu_srs import _check as check_srs
 
 RING = {"i8": ("i8_ring_128x128", "i8_ring_64x128"),
         "i16": ("i16_ring_128x128", "i16_ring_64x64")}
@@ -71,6 +73,36 @@ def test_ring_extreme_values(dt):
             for name in RING[dt]:
                 _, got = gpu_gemm(A, B, C, 40, 72, k, kernel=_kid(name))
                 assert np.array_equal(got, want), (name, k, a, b)
+
+
+# 32 and more of the small tiles: the automatic int16-output plan is the ring
+# kernel (asserted by the plan rule's test below for the same sizes).
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["i8", "i16"])
+@pytest.mark.parametrize("conv", [(0, 0, False), (0, 1, True), (0, 15, True), (0, 16, False),
+                                  (0, 16, True), (0, 17, True), (0, 17, False), (0, 24, True),
+                                  (0, 31, True), (0, 32, True), (0, 47, False), (100, 9, True),
+                                  (256, 5, False)], ids=str)
+def test_ring_srs(dt, conv):
+    kc, shift, rnd = conv
+    m, n, k = 451, 530, 300
+    from test_gpu_srs import _operands
+    A, B, C = _operands(dt, m, n, k, seed=40 + shift, pad=(1, 0, 3))
+    check_srs(A, B, C, m, n, k, kc, shift, rnd)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["i8", "i16"])
+@pytest.mark.parametrize("end", ["min", "max"])
+def test_ring_srs_extremes(dt, end):
+    """Constant operands at the types' ends over the conversion's longest
+    block (2^14): shifts on both sides of its two forms."""
+    from test_gpu_srs import _operands
+    m, n, k = 257, 1030, 1 << 14
+    v = int(getattr(np.iinfo(np.int8 if dt == "i8" else np.int16), end))
+    A, B, C = _operands(dt, m, n, k, seed=3, lo=v, hi=v)
+    for shift, rnd in ((0, False), (16, True), (17, True), (28, True), (29, False)):
+        check_srs(A, B, C, m, n, k, 0, shift, rnd)
 
 
 def test_ring_plan_rules():
