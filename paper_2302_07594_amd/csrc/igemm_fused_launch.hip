@@ -58,6 +58,7 @@ int launch_conv(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k, co
                 int gather, const void *X, const void *W, int32_t *Y, int64_t ldy,
                 void *stream) {
     (void)es;
+    if (is_ring(p.kernel)) return launch_ring(p, m, n, k, X, k, W, n, Y, ldy, &g, stream);
     if (p.kernel == K_I16_SMALL_64x64)
         return launch_small_conv(p, m, n, k, g, gather, X, W, Y, ldy, stream);
     const void *fn = conv_kernel_fn(p.kernel, gather, p.vec_b != 0, p.split > 1);

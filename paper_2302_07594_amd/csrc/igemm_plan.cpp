@@ -842,8 +842,15 @@ int make_conv_plan(int es, const igemm_conv2d_desc *d, const void *X, const void
         // The rules of the GEMM planner's fused kernels (no packed path: the
         // lowered matrix never exists).
         const int64_t ncu = num_cu > 0 ? num_cu : 256;
+        // The ring kernel: channel rows of whole 16-byte chunks at 4-byte
+        // addresses, from 2^27 multiply-adds on (below, the row tiles).
+        const bool ring = (d->c * es) % 16 == 0 && (uintptr_t)X % 4 == 0 && M > 32 &&
+                          M * N > ((int64_t)1 << 27) / K;
         if (es == 2 && (small_conv || small_runs) && small_pays(M, N, K, (int)ncu))
             id = K_I16_SMALL_64x64;
+        else if (ring && ring_plan(ring_kernel(es, M, N, K, (int)ncu, true), es, M, N, K, X, K, W,
+                                   N, N, (int)ncu, split, true, out) == IGEMM_OK)
+            id = out->kernel;
         else if (es == 2) {
             if (M <= 16) id = K_I16_16x128;
             else if (M <= 32) id = K_I16_32x128;
@@ -859,13 +866,15 @@ int make_conv_plan(int es, const igemm_conv2d_desc *d, const void *X, const void
             id = M <= 16 ? K_I8_16x256 : K_I8_32x256;
         }
     }
-    const bool conv_id = id == K_I16_128x128 || id == K_I16_64x64 || id == K_I16_32x128 ||
+    const bool conv_id = (kernel < 0 && is_ring(id)) || id == K_I16_128x128 || id == K_I16_64x64 || id == K_I16_32x128 ||
                          id == K_I16_16x128 || id == K_I8_32x256 || id == K_I8_16x256 ||
                          (id == K_I16_SMALL_64x64 && (small_conv || small_runs));
     if (!conv_id || kKernels[id].es != es) return IGEMM_EINVAL;
-    int st = make_plan(es, M, N, K, X, K, W, N, N, num_cu, id, split, false, out);
-    if (st != IGEMM_OK) return st;
-    out->vec_a = (((uintptr_t)X % 16) == 0 && (d->c * es) % 16 == 0) ? 1 : 0;
+    if (!is_ring(id)) {
+        int st = make_plan(es, M, N, K, X, K, W, N, N, num_cu, id, split, false, out);
+        if (st != IGEMM_OK) return st;
+        out->vec_a = (((uintptr_t)X % 16) == 0 && (d->c * es) % 16 == 0) ? 1 : 0;
+    }
     *gather = out->vec_a != 0 ? 1 : (runs ? 3 : 2);
     // the small-output kernel: whole taps by DMA, or runs
     if (id == K_I16_SMALL_64x64) *gather = small_conv ? 1 : 3;

@@ -1,5 +1,5 @@
-"""GPU parity of the ring kernel (mid-size products and the int16-output
-update) against the CPU oracle, bit for bit: edges of its tiles and
+"""GPU parity of the ring kernel (mid-size products, the int16-output update
+and convolutions) against the CPU oracle, bit for bit: edges of its tiles and
 k-tiles, every row alignment (DMA and register staging), k slices that end
 inside a k-tile, the conversion at shifts around its two forms, and the shapes
 where the automatic plans take it."""
@@ -8,6 +8,7 @@ import pytest
 
 import workloads
 from gpu_util import describe_mismatch, gpu_gemm, oracle_gemm
+from test_gpu_conv import _check as check_conv
 from test_gpu_srs import _check as check_srs
 
 RING = {"i8": ("i8_ring_128x128", "i8_ring_64x128"),
@@ -105,6 +106,23 @@ def test_ring_srs_extremes(dt, end):
         check_srs(A, B, C, m, n, k, 0, shift, rnd)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["i8", "i16"])
+@pytest.mark.parametrize("case", [
+    # n, h, w, c, k, r, s, stride, pad, dil
+    (9, 57, 55, 16, 96, 3, 3, (1, 1), (1, 1), (1, 1)),
+    (7, 41, 37, 48, 91, 3, 3, (2, 1), (2, 0), (2, 3)),
+    (3, 30, 30, 64, 255, 5, 3, (1, 2), (2, 1), (1, 1)),
+    (40, 28, 28, 32, 260, 1, 1, (1, 1), (0, 0), (1, 1)),
+    (2, 14, 14, 512, 130, 3, 3, (1, 1), (1, 1), (1, 1)),
+], ids=lambda c: "x".join(map(str, c[:7])))
+def test_ring_conv(dt, case):
+    n, h, w, c, k, r, s, stride, pad, dil = case
+    check_conv(dt, n, h, w, c, k, r, s, stride, pad, dil, seed=n + c)
+    # weights at an odd dword: register staging
+    check_conv(dt, n, h, w, c, k, r, s, stride, pad, dil, seed=n + k, w_off=1)
+
+
 def test_ring_plan_rules():
     """Where the automatic plans take the ring kernel and how they slice it
     (256 units, aligned buffers), and its 32-bit window limits."""
@@ -138,3 +156,9 @@ def test_ring_plan_rules():
         with pytest.raises(ig.IgemmError) as e:
             ig.igemm_query_plan(1, 256, 256, 8192, kernel=kid, **kw)
         assert e.value.status == ig.IGEMM_ENOTSUP
+    # convolutions: whole 16-byte channel chunks, from 2^27 multiply-adds
+    for es, c in ((1, 16), (2, 8)):
+        d = ig.conv_desc(32, 56, 56, c, 128, 3, 3, (1, 1), (1, 1), (1, 1))
+        assert "ring" in ig.igemm_conv2d_query_plan(es, d)["kernel_name"]
+        d = ig.conv_desc(32, 56, 56, c + 1, 128, 3, 3, (1, 1), (1, 1), (1, 1))
+        assert "ring" not in ig.igemm_conv2d_query_plan(es, d)["kernel_name"]
