@@ -2,9 +2,11 @@
 
 The functions here marshal arguments into the C ABI of ``include/igemm.h``
 with ctypes; every step of the computation runs in the HIP library. PyTorch
-is used only to hand over device pointers and the current HIP stream. There
-is no CPU fallback: the library is loaded at the first call, and that call
-raises ImportError if it is not built (``build`` is importable without it).
+is used only to hand over device pointers and the current HIP stream. The
+tensor calls below go through a compiled binding (``_igemm_torch``) in the
+plain case: checks, plan, workspace and call in one step. There is no CPU
+fallback: the libraries are loaded at the first call, and that call raises
+ImportError if they are not built (``build`` is importable without them).
 
 Same names as the C ABI:
     igemm_i16(m, n, k, A, lda, B, ldb, C, ldc, stream=None)
@@ -187,6 +189,24 @@ def load() -> None:
     """Load the HIP library now (raises ImportError if it is not built)."""
     if _Lazy._handle is None:
         _Lazy._handle = _load()
+
+
+_native = None  # the compiled binding of the tensor calls, loaded at the first one
+
+
+def _load_native():
+    """binding/igemm_torch.cpp: the plain case of the tensor calls in one step
+    (checks, plan, workspace, call). Its functions return None for anything
+    else, which the Python code below then handles."""
+    global _native
+    load()  # first, so that both bind to the library and runtime loaded there
+    try:
+        from . import _igemm_torch
+    except ImportError as e:
+        raise ImportError(f"{HERE}/_igemm_torch.so is not built or does not load ({e}); run "
+                          "`python -m paper_2302_07594_amd.build`") from e
+    _native = _igemm_torch
+    return _native
 
 
 def library_path() -> str:
@@ -545,6 +565,13 @@ def gemm_packed_b(A, PB, C, stream=None):
     """C += A.B with B packed by pack_b: A is an m x k CUDA tensor of B's
     type, C an m x n torch.int32 CUDA tensor (unit stride along rows).
     A's packed copy takes memory from torch's caching allocator. Returns C."""
+    if stream is None:
+        st = (_native or _load_native()).packed_b(PB.es, A, PB.buf, PB.nbytes, PB.n, PB.k, C,
+                                                  PB.kernel)
+        if st is not None:
+            if st != IGEMM_OK:
+                raise IgemmError(st, "gemm_packed_b")
+            return C
     import torch
     want = torch.int16 if PB.es == 2 else torch.int8
     if A.dtype != want or A.dim() != 2 or A.shape[1] != PB.k or not A.is_cuda:
@@ -576,11 +603,23 @@ def gemm_i16(A, B, C, stream=None, kernel=-1, split=-1, workspace=None):
     workspace: None / "torch" (a workspace from torch's allocator when the
     plan packs the operands), "none" (no workspace: the in-place kernels
     only) or a uint8 CUDA tensor (256-byte aligned) to use as is."""
+    if stream is None and workspace is None:
+        st = (_native or _load_native()).gemm(2, A, B, C, kernel, split)
+        if st is not None:
+            if st != IGEMM_OK:
+                raise IgemmError(st, "gemm_i16")
+            return C
     return _gemm(2, A, B, C, stream, kernel, split, workspace, "gemm_i16")
 
 
 def gemm_i8(A, B, C, stream=None, kernel=-1, split=-1, workspace=None):
     """C += A.B for 2-D torch.int8 CUDA tensors; see gemm_i16."""
+    if stream is None and workspace is None:
+        st = (_native or _load_native()).gemm(1, A, B, C, kernel, split)
+        if st is not None:
+            if st != IGEMM_OK:
+                raise IgemmError(st, "gemm_i8")
+            return C
     return _gemm(1, A, B, C, stream, kernel, split, workspace, "gemm_i8")
 
 
@@ -637,6 +676,12 @@ def gemm_srs(A, B, C, kc=0, shift=0, round_half_up=False, stream=None, kernel=-1
     (a workspace from torch's allocator when the packed path is taken, so the
     call may be captured into a graph), 'none' (fused kernels only) or a
     uint8 tensor. Returns C."""
+    if stream is None and workspace is None:
+        st = (_native or _load_native()).srs(A, B, C, kc, shift, round_half_up, kernel)
+        if st is not None:
+            if st != IGEMM_OK:
+                raise IgemmError(st, "gemm_srs")
+            return C
     import torch
     if A.dtype not in (torch.int16, torch.int8) or B.dtype != A.dtype:
         raise TypeError("gemm_srs: A and B must both be torch.int16 or both torch.int8")
@@ -708,6 +753,12 @@ def conv2d(X, W, Y, stride=(1, 1), pad=(0, 0), dil=(1, 1), stream=None, kernel=-
     """Y += conv(X, W) on contiguous CUDA tensors: X n x h x w x c and W
     r x s x c x k (both torch.int16 or both torch.int8), Y n x oh x ow x k
     torch.int32. Returns Y; raises IgemmError on a bad status."""
+    if stream is None:
+        st = (_native or _load_native()).conv2d(X, W, Y, stride, pad, dil, kernel, split)
+        if st is not None:
+            if st != IGEMM_OK:
+                raise IgemmError(st, "conv2d")
+            return Y
     import torch
     if X.dtype not in (torch.int16, torch.int8) or W.dtype != X.dtype:
         raise TypeError("conv2d: X and W must both be torch.int16 or both torch.int8")

@@ -3,7 +3,9 @@
 ``python -m paper_2302_07594_amd.build`` (or ``build()``) compiles
 ``csrc/*.hip`` and ``csrc/*.cpp`` with hipcc into
 ``paper_2302_07594_amd/libigemm.so``. The library exports the C ABI declared
-in ``include/igemm.h``.
+in ``include/igemm.h``. ``binding/igemm_torch.cpp``, the tensor calls' native
+path, is compiled with g++ against torch's headers and that library into
+``paper_2302_07594_amd/_igemm_torch.so``.
 
 Next to the library, ``libigemm.so.sha256`` records the SHA-256 of every
 source, header and compiler flag the library was built from
@@ -15,10 +17,12 @@ from __future__ import annotations
 import concurrent.futures
 import glob
 import hashlib
+import importlib.util
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -27,6 +31,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libigemm.so")
 STAMP = LIB + ".sha256"
+BINDING_SRC = os.path.join(HERE, "binding", "igemm_torch.cpp")
+BINDING = os.path.join(HERE, "_igemm_torch.so")
 ARCH = "gfx950"
 
 # Packed fp32 instructions are kept out of every HIP build of this library.
@@ -69,7 +75,7 @@ def _hash_files(paths, flags) -> str:
 
 def source_hash(extra_flags=None) -> str:
     """SHA-256 over every source and header of the library and the flags."""
-    return _hash_files(sources() + headers(), compile_flags(extra_flags))
+    return _hash_files(sources() + headers() + [BINDING_SRC], compile_flags(extra_flags))
 
 
 # Everything the packed multiply kernel is built from (its source and the
@@ -107,7 +113,7 @@ def is_current() -> bool:
             stamp = f.read().strip()
     except OSError:
         return False
-    return os.path.exists(LIB) and stamp == source_hash()
+    return os.path.exists(LIB) and os.path.exists(BINDING) and stamp == source_hash()
 
 
 def _run(cmd, verbose):
@@ -117,9 +123,25 @@ def _run(cmd, verbose):
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
     if res.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({res.returncode}):\n{err}")
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed ({res.returncode}):\n{err}")
     if verbose and err.strip():
         print(err, file=sys.stderr)
+
+
+def _build_binding(verbose: bool) -> None:
+    """Compile binding/igemm_torch.cpp against torch and the built library."""
+    torch_dir = list(importlib.util.find_spec("torch").submodule_search_locations)[0]
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    inc = [INCLUDE, os.path.join(torch_dir, "include"),
+           os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
+           os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    tmp = BINDING + ".tmp"
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1",
+          "-DUSE_ROCM"] + [f for d in inc for f in ("-I", d)] +
+         [BINDING_SRC, "-o", tmp, "-L", os.path.join(torch_dir, "lib"), "-ltorch_python",
+          "-ltorch_hip", "-ltorch_cpu", "-lc10_hip", "-lc10", "-L", HERE,
+          "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN"], verbose)
+    os.replace(tmp, BINDING)
 
 
 def build(verbose: bool = False, extra_flags=None, jobs: int = 0, object_cache=None) -> str:
@@ -160,6 +182,7 @@ def build(verbose: bool = False, extra_flags=None, jobs: int = 0, object_cache=N
         _run([hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC"] + objs + ["-o", tmp],
              verbose)
     os.replace(tmp, LIB)
+    _build_binding(verbose)
     with open(STAMP, "w") as f:
         f.write(source_hash(extra_flags) + "\n")
     return LIB
