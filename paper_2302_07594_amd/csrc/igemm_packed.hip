@@ -363,8 +363,12 @@ pack_b(const void *__restrict__ Bv, int64_t ldb, int k, int n, int k_pad, int ks
 // SKIPZ (short k, one k range): kcb counts the k-tiles that hold data, and the
 // MFMAs of the zero-padding tiles past them are skipped (RAGGED's run-time
 // tail needs more registers than eight waves have).
+// SLICED (int32 update): the grid is a number of k slices times the tiles;
+// slice z multiplies kcb k-tiles (a multiple of four) from z kcb on, the last
+// one what is left of ktiles, and adds into C with 32-bit atomic adds; the
+// corrections go with the first slice.
 template <int ES, int BM, int BN, int WM, int WN, int NST, int EPI = 0, bool RAGGED = false,
-          bool SKIPZ = false>
+          bool SKIPZ = false, bool SLICED = false>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64, 1)
 igemm_packed(const int8_t *__restrict__ Ap, int64_t lda_p,
              const int8_t *__restrict__ Bp, int64_t ldb_p,
@@ -407,6 +411,7 @@ igemm_packed(const int8_t *__restrict__ Ap, int64_t lda_p,
     constexpr int SMODE = EPI - 2;
     static_assert(!MULTI || !RAGGED, "blocks of whole groups of four k-tiles");
     static_assert(!SKIPZ || (!MULTI && !RAGGED), "zero tiles skipped in one k range");
+    static_assert(!SLICED || (EPI == 0 && !RAGGED && !SKIPZ && NST == 4), "k slices, int32 update");
     constexpr int MAXB = 16;  // blocks of one multi-block launch
 
     // The LDS stages as separate objects, so that the compiler can tell the
@@ -430,7 +435,16 @@ igemm_packed(const int8_t *__restrict__ Ap, int64_t lda_p,
     const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
 
     int bid = blockIdx.x;
-    const int G = gridDim.x;
+    int G = gridDim.x;
+    if constexpr (SLICED) {
+        G = tiles_m * tiles_n;
+        const int z = bid / G;
+        bid -= z * G;
+        Ap += (int64_t)(z * kcb) * RB;
+        Bp += (int64_t)(z * kcb) * RB;
+        ktiles = min(kcb, ktiles - z * kcb);
+        if (z > 0) corrA = nullptr;
+    }
     if ((G & 7) == 0) bid = (bid & 7) * (G >> 3) + (bid >> 3);
     constexpr int GROUP = 8;
     const int span = GROUP * tiles_n;
@@ -933,6 +947,25 @@ igemm_packed(const int8_t *__restrict__ Ap, int64_t lda_p,
             }
         }
     };
+    if constexpr (SLICED) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int lc = wn0 + MF * j + M::out_col(lane);
+#pragma unroll
+                for (int r = 0; r < M::REGS; ++r) {
+                    const int lr = wm0 + MF * i + M::out_row(lane, r);
+                    u32 v = (u32)acc[0][i][j][r];
+                    if constexpr (ES == 2)
+                        v = 65536u * v + 256u * (u32)acc[1][i][j][r] + (u32)acc[2][i][j][r] +
+                            colt[j] + rowt[i][r];
+                    if (m0 + lr < m && n0 + lc < n)
+                        atomicAdd(C + (int64_t)(m0 + lr) * ldc + (n0 + lc), (int)v);
+                }
+            }
+        return;
+    }
     load_batch(ic<0>{}, ic<0>{});
     auto epi_step = [&](auto batch) {
         constexpr int BT = decltype(batch)::value;
@@ -1128,6 +1161,27 @@ int launch_srs_packed(const igemm_plan &p, int64_t m, int64_t n, int64_t k, int6
     return IGEMM_OK;
 }
 
+// k-tiles per slice (a multiple of four) of a multiply of `tiles` tiles, or
+// ktiles for one slice. One workgroup fits on a compute unit, so with at most
+// half as many tiles as units the rest would idle: slices up to one workgroup
+// per unit, as long as the k-tiles they save (about 0.8 us each, 0.65 int8)
+// outweigh their atomic adds into C (about 2.4 us per million). (With more than
+// half, slices in a second round, spread over the idle units, lost: 172 tiles
+// 75 us against 65.)
+static int slice_tiles(int es, int64_t m, int64_t n, int64_t tiles, int ktiles, int num_cu) {
+    int best = ktiles;
+    double best_t = (es == 2 ? 0.8 : 0.65) * ktiles;
+    for (int64_t s = 2; s * tiles <= num_cu && 4 * s <= ktiles; ++s) {
+        const int per = (int)((ktiles / 4 + s - 1) / s) * 4;
+        const double t = (es == 2 ? 0.8 : 0.65) * per + 2.4e-6 * (double)m * (double)n * (double)s;
+        if (t < best_t) {
+            best_t = t;
+            best = per;
+        }
+    }
+    return best;
+}
+
 int launch_multiply(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k, const void *A,
                     int64_t lda, int32_t *C, int64_t ldc, const void *a_part, const void *b_part,
                     void *stream_) {
@@ -1169,11 +1223,21 @@ int launch_multiply(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k
         int ktiles = (int)(kc / 64);
         const int kr = (int)((real + 63) / 64);
         const bool ragged = es == 2 && kr % 4 == 1 && kr > 4 && kr < ktiles;
-        if (ragged) ktiles = kr;
         const bool first = k0 == 0;
         const uint32_t *cA = first ? corrA : nullptr;
         const uint32_t kc16 = first ? 16384u * (uint32_t)k : 0u;
-        if (es == 2 && ragged)
+        const int per = slice_tiles(es, m, n, p.tiles, ktiles, 256);
+        const dim3 sgrid((unsigned)(p.tiles * ((ktiles + per - 1) / per)));
+        if (ragged && per == ktiles) ktiles = kr;
+        if (per < (int)(kc / 64) && es == 2)
+            igemm_packed<2, 128, 128, 64, 64, 4, 0, false, false, true><<<sgrid, 256, 0, stream>>>(
+                Asrc + 2 * k0, lda_p, Bpk + 2 * k0, ldb_p, cA, corrB, kc16, C, ldc, mi, ni,
+                ktiles, tm, tn, 0, per);
+        else if (per < (int)(kc / 64))
+            igemm_packed<1, 256, 256, 64, 128, 4, 0, false, false, true>
+                <<<sgrid, 512, 0, stream>>>(Asrc + k0, lda_p, Bpk + k0, ldb_p, nullptr, nullptr,
+                                            0u, C, ldc, mi, ni, ktiles, tm, tn, 0, per);
+        else if (es == 2 && ragged)
             igemm_packed<2, 128, 128, 64, 64, 4, 0, true><<<grid, 256, 0, stream>>>(
                 Asrc + 2 * k0, lda_p, Bpk + 2 * k0, ldb_p, cA, corrB, kc16, C, ldc, mi, ni, ktiles, tm, tn, 0);
         else if (es == 2)
