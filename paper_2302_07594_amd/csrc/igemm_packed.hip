@@ -434,18 +434,23 @@ igemm_packed(const int8_t *__restrict__ Ap, int64_t lda_p,
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm0 = (wave / WGN) * WM, wn0 = (wave % WGN) * WN;
 
+    // Workgroup ids go to the eight XCDs in turn: each takes a contiguous range
+    // of (slice and) tiles, so that tiles that share operand rows meet in one
+    // L2 (172 tiles, two to each column block of B: 61.8 us against 65.6 when
+    // only grids of whole eights were renumbered).
     int bid = blockIdx.x;
-    int G = gridDim.x;
+    {
+        const int G = gridDim.x, x = bid & 7;
+        bid = x * (G >> 3) + min(x, G & 7) + (bid >> 3);
+    }
     if constexpr (SLICED) {
-        G = tiles_m * tiles_n;
-        const int z = bid / G;
-        bid -= z * G;
+        const int tiles = tiles_m * tiles_n, z = bid / tiles;
+        bid -= z * tiles;
         Ap += (int64_t)(z * kcb) * RB;
         Bp += (int64_t)(z * kcb) * RB;
         ktiles = min(kcb, ktiles - z * kcb);
         if (z > 0) corrA = nullptr;
     }
-    if ((G & 7) == 0) bid = (bid & 7) * (G >> 3) + (bid >> 3);
     constexpr int GROUP = 8;
     const int span = GROUP * tiles_n;
     const int first_m = (bid / span) * GROUP;
