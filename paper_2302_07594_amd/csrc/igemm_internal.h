@@ -219,7 +219,8 @@ int launch_ring(const igemm_plan &p, int64_t m, int64_t n, int64_t k, const void
 int launch_ring_srs(const igemm_plan &p, int64_t m, int64_t n, int64_t k, const void *A,
                     int64_t lda, const void *B, int64_t ldb, int16_t *C, int64_t ldc, int shift,
                     int round_half_up, void *stream);
-const void *ring_i8(int id, bool conv, bool reg, int epi);
+// (one_per_cu: the grid has at most one workgroup per compute unit)
+const void *ring_i8(int id, bool conv, bool reg, int epi, bool one_per_cu);
 const void *ring_i16(int id, bool conv, int epi);
 // The small-output int16 kernel: one launch, k slices of plan.k_chunk; and
 // its convolution variants (A gathered from X: gather 1, whole 64-channel

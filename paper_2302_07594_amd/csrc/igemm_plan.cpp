@@ -358,6 +358,13 @@ bool is_ring(int id) {
            id == K_I16_RING_64x64;
 }
 
+// The ring kernel stages by DMA: int8 whose rows start at 4-byte addresses (a
+// convolution's input at one).
+static bool ring_dma(int es, const void *A, int64_t lda, const void *B, int64_t ldb, bool conv) {
+    return es == 1 && (uintptr_t)A % 4 == 0 && (uintptr_t)B % 4 == 0 &&
+           (conv || lda % 4 == 0) && ldb % 4 == 0;
+}
+
 // Modelled time (us, without the launch) of a ring kernel with s k slices,
 // fitted to its measured times on 256 compute units: `r` workgroups per unit
 // share it, each k-tile (128 int8, 64 int16) costs the unit a fixed part and
@@ -368,39 +375,45 @@ bool is_ring(int id) {
 // 11.3 / 11.7 / 16.7, 128 x 128 tiles 512 x 4096 x 4096 55.0 / 43.3 / 54.4.
 // Tile shapes: int8 2048 x 4096 x 4096 50.0 with 128 x 128 against 64.5 with
 // 64 x 128, 1536^3 17.0 against 13.9; int16 1024 x 4096 x 4096 74.8 with 128 x
-// 128 against 94.3 with 64 x 64, 1024^3 16.4 against 11.3.
-static double ring_time(int id, int64_t m, int64_t n, int64_t k, int64_t s, int num_cu) {
+// 128 against 94.3 with 64 x 64, 1024^3 16.4 against 11.3. int8 through registers (not
+// dma) 1000 x 3001 x 1777 20.4 with 128 x 128 against 23.7, 777 x 1111 x 2049 19.0
+// against 14.4.
+static double ring_time(int id, bool dma, int64_t m, int64_t n, int64_t k, int64_t s,
+                        int num_cu) {
     const KernelDesc &d = kKernels[id];
     const int64_t kt = cdiv(cdiv(k, 128 / d.es), s);
     const double r = (double)cdiv(tiles_of(id, m, n) * s, num_cu);
     double t = 0;
     switch (id) {
         case K_I8_RING_128x128: t = 2.0 + (0.4 + 0.5 * r) * kt; break;
-        case K_I8_RING_64x128: t = 0.47 * r * kt; break;
+        case K_I8_RING_64x128: t = (dma ? 0.47 : 0.6) * r * kt; break;
         case K_I16_RING_128x128: t = 2.0 + 0.95 * r * kt; break;
         default: t = (0.22 + 0.28 * r) * kt; break;  // K_I16_RING_64x64
     }
-    return t + (s > 1 ? 2.4e-6 * (double)m * (double)n * (double)s : 0.0);
+    return t + (s > 1 ? 0.7 + 2.4e-6 * (double)m * (double)n * (double)s : 0.0);
 }
 
 // The slice count with the least modelled time.
-static int64_t ring_split(int id, int64_t m, int64_t n, int64_t k, int num_cu) {
+static int64_t ring_split(int id, bool dma, int64_t m, int64_t n, int64_t k, int num_cu) {
     const int64_t ktiles = cdiv(k, 128 / kKernels[id].es);
     int64_t best = 1;
     for (int64_t s = 2; s <= 16 && s <= ktiles; ++s)
-        if (ring_time(id, m, n, k, s, num_cu) < ring_time(id, m, n, k, best, num_cu)) best = s;
+        if (ring_time(id, dma, m, n, k, s, num_cu) < ring_time(id, dma, m, n, k, best, num_cu))
+            best = s;
     return best;
 }
 
 // The ring kernel (tile shape) with the least modelled time; sliced: k slices
 // are allowed.
-static int ring_kernel(int es, int64_t m, int64_t n, int64_t k, int num_cu, bool sliced) {
+static int ring_kernel(int es, bool dma, int64_t m, int64_t n, int64_t k, int num_cu,
+                       bool sliced) {
     const int big = es == 2 ? K_I16_RING_128x128 : K_I8_RING_128x128;
     const int small = es == 2 ? K_I16_RING_64x64 : K_I8_RING_64x128;
-    const int64_t sb = sliced ? ring_split(big, m, n, k, num_cu) : 1;
-    const int64_t ss = sliced ? ring_split(small, m, n, k, num_cu) : 1;
-    return ring_time(big, m, n, k, sb, num_cu) < ring_time(small, m, n, k, ss, num_cu) ? big
-                                                                                       : small;
+    const int64_t sb = sliced ? ring_split(big, dma, m, n, k, num_cu) : 1;
+    const int64_t ss = sliced ? ring_split(small, dma, m, n, k, num_cu) : 1;
+    return ring_time(big, dma, m, n, k, sb, num_cu) < ring_time(small, dma, m, n, k, ss, num_cu)
+               ? big
+               : small;
 }
 
 // The ring kernel's plan: any alignment and any size whose windows take its
@@ -419,25 +432,24 @@ static int ring_plan(int id, int es, int64_t m, int64_t n, int64_t k, const void
     const int64_t tiles = cdiv(m, d.bm) * cdiv(n, d.bn);
     // (an explicit slice count is honoured in units of 64)
     const int64_t unit = split > 0 ? kBK : bk, units = cdiv(k, unit);
-    int64_t s = split > 0 ? split : ring_split(id, m, n, k, num_cu);
+    const bool aligned = ring_dma(es, A, lda, B, ldb, conv);
+    int64_t s = split > 0 ? split : ring_split(id, aligned, m, n, k, num_cu);
     if (s < cdiv(k, kMaxKChunk)) s = cdiv(k, kMaxKChunk);
     if (s > units) s = units;
     out->k_chunk = cdiv(units, s) * unit;
     s = cdiv(k, out->k_chunk);
     int64_t grid;
     if (!mul_ok(tiles, s, &grid) || grid > kMaxGrid) return IGEMM_ENOTSUP;
-    // int8 by DMA: rows at 4-byte addresses, the k range's rows of B in one
-    // window.
-    const uintptr_t a = (uintptr_t)A, b = (uintptr_t)B;
-    const bool dma = es == 1 && a % 4 == 0 && b % 4 == 0 && (conv || lda % 4 == 0) &&
-                     ldb % 4 == 0 && b_row < lim / (out->k_chunk + bk) - 16;
+    // (by DMA the k range's rows of B lie in one window)
+    const bool dma = aligned && b_row < lim / (out->k_chunk + bk) - 16;
     out->kernel = id;
     out->elem_bytes = es;
     out->limb_products = es == 2 ? 4 : 1;
     out->bm = d.bm;
     out->bn = d.bn;
     out->bk = (int)bk;
-    out->threads = (d.bm / d.wm) * (d.bn / d.wn) * 64;
+    // (int8 through registers: waves of half the columns, twice as many)
+    out->threads = (d.bm / d.wm) * (d.bn / d.wn) * 64 * (es == 1 && !dma ? 2 : 1);
     out->split = (int)s;
     out->tiles = tiles;
     out->grid = grid;
@@ -481,7 +493,8 @@ static int auto_kernel(int es, int64_t m, int64_t n, int64_t k, const void *A, i
     // 201 x 6001 10.3 against 17.9, 146 x 97 x 792 5.9 against 5.1).
     igemm_plan rp{};
     if (m > 32) {
-        const int rid = ring_kernel(es, m, n, k, num_cu, true);
+        const int rid =
+            ring_kernel(es, ring_dma(es, A, lda, B, ldb, false), m, n, k, num_cu, true);
         if (ring_plan(rid, es, m, n, k, A, lda, B, ldb, ldc, num_cu, -1, false, &rp) == IGEMM_OK) {
             const int64_t t = tiles_of(es == 2 ? K_I16_RING_64x64 : K_I8_RING_64x128, m, n);
             if (es == 1 ? (rp.vec_a != 0 || t >= 32) : (k > kBK && (t >= 32 || k >= 2048)))
@@ -763,8 +776,8 @@ int make_srs_plan(int es, int64_t m, int64_t n, int64_t kb, const void *A, int64
     // (its int16 conversion's bound).
     if (id < 0 && m > 32 && kb <= (1 << 14) &&
         tiles_of(es == 2 ? K_I16_RING_64x64 : K_I8_RING_64x128, m, n) >= 32 &&
-        ring_plan(ring_kernel(es, m, n, kb, num_cu, false), es, m, n, kb, A, lda, B, ldb, ldc,
-                  num_cu, 1, false, out) == IGEMM_OK)
+        ring_plan(ring_kernel(es, ring_dma(es, A, lda, B, ldb, false), m, n, kb, num_cu, false),
+                  es, m, n, kb, A, lda, B, ldb, ldc, num_cu, 1, false, out) == IGEMM_OK)
         return IGEMM_OK;
     if (id < 0) {
         if (es == 2)
@@ -848,8 +861,10 @@ int make_conv_plan(int es, const igemm_conv2d_desc *d, const void *X, const void
                           M * N > ((int64_t)1 << 27) / K;
         if (es == 2 && (small_conv || small_runs) && small_pays(M, N, K, (int)ncu))
             id = K_I16_SMALL_64x64;
-        else if (ring && ring_plan(ring_kernel(es, M, N, K, (int)ncu, true), es, M, N, K, X, K, W,
-                                   N, N, (int)ncu, split, true, out) == IGEMM_OK)
+        else if (ring && ring_plan(ring_kernel(es, ring_dma(es, X, 0, W, N, true), M, N, K,
+                                               (int)ncu, true),
+                                   es, M, N, K, X, K, W, N, N, (int)ncu, split, true, out) ==
+                             IGEMM_OK)
             id = out->kernel;
         else if (es == 2) {
             if (M <= 16) id = K_I16_16x128;

@@ -14,7 +14,8 @@ int launch(const igemm_plan &p, int64_t m, int64_t n, int64_t k, const void *A, 
            int epi, void *stream) {
     const bool reg = p.vec_a == 0;
     const void *fn = kKernels[p.kernel].es == 2 ? ring_i16(p.kernel, g != nullptr, epi_kind)
-                                                : ring_i8(p.kernel, g != nullptr, reg, epi_kind);
+                                                : ring_i8(p.kernel, g != nullptr, reg, epi_kind,
+                                                          p.grid <= 256);
     if (fn == nullptr) return IGEMM_EINVAL;
     int mi = (int)m, ni = (int)n, ki = (int)k, kc = (int)p.k_chunk;
     int tm = (int)((m + p.bm - 1) / p.bm), tn = (int)((n + p.bn - 1) / p.bn);
