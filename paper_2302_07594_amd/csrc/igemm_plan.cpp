@@ -390,7 +390,7 @@ static double ring_time(int id, bool dma, int64_t m, int64_t n, int64_t k, int64
         case K_I16_RING_128x128: t = 2.0 + 0.95 * r * kt; break;
         default: t = (0.22 + 0.28 * r) * kt; break;  // K_I16_RING_64x64
     }
-    return t + (s > 1 ? 0.7 + 2.4e-6 * (double)m * (double)n * (double)s : 0.0);
+    return t + (s > 1 ? 2.4e-6 * (double)m * (double)n * (double)s : 0.0);
 }
 
 // The slice count with the least modelled time.
