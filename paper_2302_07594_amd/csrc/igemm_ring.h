@@ -167,10 +167,13 @@ igemm_ring(const char *__restrict__ A, int64_t lda, const char *__restrict__ B, 
     static_assert(!REG || NST == 2, "two stages through registers");
     static_assert(ES == 1 || REG, "int16 is split on its way through registers");
     static_assert(ES == 1 || WGN >= 2, "int16: 2 x 2 waves share the sums");
-    static_assert(OCC * (NST * STAGE + (ES == 2 ? 4 * (BM + BN) : 0)) <= 160 * 1024, "LDS");
+    // int16: a sum per row and column of the tile; the int16-output update keeps
+    // two terms of each (below).
+    constexpr int NSUM = ES == 2 ? (BM + BN) * (EPI == EPI_SRS ? 2 : 1) : 4;
+    static_assert(OCC * (NST * STAGE + 4 * NSUM) <= 160 * 1024, "LDS");
 
     __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE];
-    __shared__ __attribute__((aligned(16))) int sums[ES == 2 ? BM + BN : 4];
+    __shared__ __attribute__((aligned(16))) int sums[NSUM];
 
     // Named up front so that the argument loads issue together.
     asm volatile("" ::"s"(A), "s"(lda), "s"(B), "s"(ldb), "s"(C), "s"(ldc), "s"(m), "s"(n),
@@ -583,8 +586,15 @@ igemm_ring(const char *__restrict__ A, int64_t lda, const char *__restrict__ B, 
         for (int i = 0; i < NPS; ++i) {
             // sum of the 256 h + l' (the 128 per element goes into the constant)
             const int w = 256 * sum_h[i] + sum_l[i], v = w + __shfl_xor(w, 32);
-            if (lane < 32 && i < (rows_wave ? TM : TN))
-                sums[rows_wave ? wm0 + 32 * i + lane : BM + wn0 + 32 * i + lane] = v;
+            if (lane < 32 && i < (rows_wave ? TM : TN)) {
+                const int at = rows_wave ? wm0 + 32 * i + lane : BM + wn0 + 32 * i + lane;
+                if constexpr (EPI == EPI_SRS) {
+                    sums[at] = v >> 1;
+                    sums[BM + BN + at] = 128 * (v & 1);
+                } else {
+                    sums[at] = v;
+                }
+            }
         }
         __syncthreads();
     }
@@ -600,31 +610,43 @@ igemm_ring(const char *__restrict__ A, int64_t lda, const char *__restrict__ B, 
     // 32 bits, the unit is added with saturation (beyond 2^31 the result
     // saturates too), then the shift. Shifts from 16 on drop the low 16 bits:
     // (z + rounding) >> (shift - 16), where the rounding of shift 16 is bit 15
-    // of v. int8: v fits in 30 bits; shifts above 31 act as 31, and the
+    // of v; shift 0 needs neither rounding nor a shift. R / 2 and 128 (R % 2) of a
+    // row, and of a column, are formed once, where the sum is, and read from
+    // LDS: the conversion was almost half of the kernel's vector instructions,
+    // which bound it (rocprofv3: 12.1 million, 40 % of the cycles, against 17 %
+    // for the matrix cores); with both, (4096, 4096, 290) 45.8 us to 43.5,
+    // (4065, 670, 1213) in blocks of 290 53.7 to 52.4. int8: v fits in 30 bits; shifts above 31 act as 31, and the
     // rounding unit of 31 already rounds every v to 0.
     const int shift = epi & 0xff;
     const bool round = ((epi >> 8) & 1) != 0 && shift > 0;
-    auto update = [&](auto wide_c) __attribute__((always_inline)) {
-        constexpr bool WIDE = decltype(wide_c)::value != 0;  // shift >= 16
+    auto update = [&](auto mode_c) __attribute__((always_inline)) {
+        constexpr bool WIDE = decltype(mode_c)::value == 1;  // shift >= 16
+        constexpr bool NOSH = decltype(mode_c)::value == 2;  // shift 0
         const int sh = ES == 1 ? min(shift, 31) : (WIDE ? shift - 16 : shift);
         const int half = round && sh > 0 ? (int)(1u << (sh - 1)) : 0;
         const int bit15 = round && sh == 0 ? 1 : 0;  // WIDE: shift 16
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            int rowt[M::REGS];
-            if constexpr (ES == 2) {
+            int rowt[M::REGS], rowl[M::REGS];
+            auto row_terms = [&](int (&t)[M::REGS], int at) __attribute__((always_inline)) {
 #pragma unroll
                 for (int r = 0; r < M::REGS; r += 4) {
-                    const int4 q = *(const int4 *)(sums + wm0 + 32 * i + M::out_row(lane, r));
-                    rowt[r] = q.x;
-                    rowt[r + 1] = q.y;
-                    rowt[r + 2] = q.z;
-                    rowt[r + 3] = q.w;
+                    const int4 q = *(const int4 *)(sums + at + wm0 + 32 * i + M::out_row(lane, r));
+                    t[r] = q.x;
+                    t[r + 1] = q.y;
+                    t[r + 2] = q.z;
+                    t[r + 3] = q.w;
                 }
-            }
+            };
+            if constexpr (ES == 2) row_terms(rowt, 0);
+            if constexpr (ES == 2 && EPI == EPI_SRS) row_terms(rowl, BM + BN);
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 const int colt = ES == 2 ? sums[BM + wn0 + 32 * j + M::out_col(lane)] : 0;
+                const int coll =
+                    ES == 2 && EPI == EPI_SRS
+                        ? sums[BM + BN + BM + wn0 + 32 * j + M::out_col(lane)] + 16384 * kmul
+                        : 0;
 #pragma unroll
                 for (int r = 0; r < M::REGS; ++r) {
                     const int a0 = acc[0][i][j][r];
@@ -633,10 +655,8 @@ igemm_ring(const char *__restrict__ A, int64_t lda, const char *__restrict__ B, 
                         if constexpr (ES == 1) {
                             t = (a0 + half) >> sh;
                         } else {
-                            const int l = acc[2][i][j][r] + 128 * ((rowt[r] & 1) + (colt & 1)) +
-                                          16384 * kmul;
-                            const int y =
-                                acc[1][i][j][r] + (rowt[r] >> 1) + (colt >> 1) + (l >> 8);
+                            const int l = acc[2][i][j][r] + rowl[r] + coll;
+                            const int y = acc[1][i][j][r] + rowt[r] + colt + (l >> 8);
                             const int z = a0 + (y >> 8);
                             if constexpr (WIDE) {
                                 t = (z + half + ((y >> 7) & bit15)) >> sh;
@@ -644,7 +664,8 @@ igemm_ring(const char *__restrict__ A, int64_t lda, const char *__restrict__ B, 
                                 const u32 zc = (u32)min(max(z, -32768), 32767);
                                 const u32 v = perm(zc, perm((u32)y, (u32)l, 0x0c0c0400u),
                                                    0x05040100u);
-                                t = __builtin_elementwise_add_sat((int)v, half) >> sh;
+                                t = NOSH ? (int)v
+                                         : __builtin_elementwise_add_sat((int)v, half) >> sh;
                             }
                         }
                         t = min(max(t, -32768), 32767);
@@ -672,6 +693,8 @@ igemm_ring(const char *__restrict__ A, int64_t lda, const char *__restrict__ B, 
     };
     if (EPI == EPI_SRS && ES == 2 && shift >= 16)
         update(ic<1>{});
+    else if (EPI == EPI_SRS && ES == 2 && shift == 0)
+        update(ic<2>{});
     else
         update(ic<0>{});
 }
