@@ -850,6 +850,7 @@ int make_conv_plan(int es, const igemm_conv2d_desc *d, const void *X, const void
                             small_ok(M, N, K, X, K, W, N, N);
     const bool small_runs = es == 2 && !small_conv && runs &&
                             small_rg_ok(M, N, K, X, K, W, N, N);
+    if (split < -1 || split == 0) return IGEMM_EINVAL;
     int id = kernel;
     if (id < 0) {
         // The rules of the GEMM planner's fused kernels (no packed path: the
@@ -881,8 +882,9 @@ int make_conv_plan(int es, const igemm_conv2d_desc *d, const void *X, const void
             id = M <= 16 ? K_I8_16x256 : K_I8_32x256;
         }
     }
-    const bool conv_id = (kernel < 0 && is_ring(id)) || id == K_I16_128x128 || id == K_I16_64x64 || id == K_I16_32x128 ||
-                         id == K_I16_16x128 || id == K_I8_32x256 || id == K_I8_16x256 ||
+    const bool conv_id = (kernel < 0 && is_ring(id)) || id == K_I16_128x128 ||
+                         id == K_I16_64x64 || id == K_I16_32x128 || id == K_I16_16x128 ||
+                         id == K_I8_32x256 || id == K_I8_16x256 ||
                          (id == K_I16_SMALL_64x64 && (small_conv || small_runs));
     if (!conv_id || kKernels[id].es != es) return IGEMM_EINVAL;
     if (!is_ring(id)) {

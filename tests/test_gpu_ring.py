@@ -162,3 +162,19 @@ def test_ring_plan_rules():
         assert "ring" in ig.igemm_conv2d_query_plan(es, d)["kernel_name"]
         d = ig.conv_desc(32, 56, 56, c + 1, 128, 3, 3, (1, 1), (1, 1), (1, 1))
         assert "ring" not in ig.igemm_conv2d_query_plan(es, d)["kernel_name"]
+
+
+def test_conv_slice_counts_refused():
+    """A slice count that is neither -1 nor at least 1 is refused, whichever
+    kernel the automatic plan takes: the ring kernel (64 channels, batch 32),
+    a fused one (63 channels) or the small-output kernel (batch 1)."""
+    ig = _ig()
+    for es in (1, 2):
+        for n, c in ((32, 64), (32, 63), (1, 64)):
+            d = ig.conv_desc(n, 14, 14, c, 256, 3, 3, (1, 1), (1, 1), (1, 1))
+            for split in (-1, 1, 3):
+                assert ig.igemm_conv2d_query_plan(es, d, split=split)["grid"] > 0
+            for split in (0, -2, -5):
+                with pytest.raises(ig.IgemmError) as e:
+                    ig.igemm_conv2d_query_plan(es, d, split=split)
+                assert e.value.status == ig.IGEMM_EINVAL, (es, n, c, split)
