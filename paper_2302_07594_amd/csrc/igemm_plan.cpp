@@ -37,8 +37,8 @@ const KernelDesc kKernels[K_COUNT] = {
     {"i16_ring_64x64", 2, 64, 64, 32, 32, false},
 };
 
-// Largest grid (in workgroups) of one launch: the dispatch packet counts
-// work-items in 32 bits.
+// Largest grid (in workgroups) of one launch of 256 threads: the dispatch packet
+// counts work-items in 32 bits. (Kernels of more threads have bounds of their own.)
 static constexpr int64_t kMaxGrid = ((int64_t)1 << 32) / kThreads - 1;
 
 static bool mul_ok(int64_t a, int64_t b, int64_t *out) {
@@ -438,18 +438,20 @@ static int ring_plan(int id, int es, int64_t m, int64_t n, int64_t k, const void
     if (s > units) s = units;
     out->k_chunk = cdiv(units, s) * unit;
     s = cdiv(k, out->k_chunk);
-    int64_t grid;
-    if (!mul_ok(tiles, s, &grid) || grid > kMaxGrid) return IGEMM_ENOTSUP;
     // (by DMA the k range's rows of B lie in one window)
     const bool dma = aligned && b_row < lim / (out->k_chunk + bk) - 16;
+    // (int8 through registers: waves of half the columns, twice as many)
+    const int threads = (d.bm / d.wm) * (d.bn / d.wn) * 64 * (es == 1 && !dma ? 2 : 1);
+    int64_t grid;
+    if (!mul_ok(tiles, s, &grid) || grid > (((int64_t)1 << 32) - 1) / threads)
+        return IGEMM_ENOTSUP;
     out->kernel = id;
     out->elem_bytes = es;
     out->limb_products = es == 2 ? 4 : 1;
     out->bm = d.bm;
     out->bn = d.bn;
     out->bk = (int)bk;
-    // (int8 through registers: waves of half the columns, twice as many)
-    out->threads = (d.bm / d.wm) * (d.bn / d.wn) * 64 * (es == 1 && !dma ? 2 : 1);
+    out->threads = threads;
     out->split = (int)s;
     out->tiles = tiles;
     out->grid = grid;

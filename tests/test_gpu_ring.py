@@ -178,3 +178,23 @@ def test_conv_slice_counts_refused():
                 with pytest.raises(ig.IgemmError) as e:
                     ig.igemm_conv2d_query_plan(es, d, split=split)
                 assert e.value.status == ig.IGEMM_EINVAL, (es, n, c, split)
+
+
+@pytest.mark.parametrize("es,m,n,k", [(1, 1200000000, 1, 1), (1, 1200000000, 3, 5),
+                                      (1, 1, 1200000000, 1), (1, 1100000000, 1, 3),
+                                      (1, 300, 1100000000, 300), (2, 1100000000, 100, 300)])
+def test_plans_fit_one_dispatch(es, m, n, k):
+    """Work-items of one launch (workgroups times the plan's own threads) are
+    counted in 32 bits: products of a billion rows or columns, whose ring
+    forms of 512 threads would exceed that, keep a kernel that fits."""
+    ig = _ig()
+    for base in (0x10000, 0x10001 if es == 1 else 0x10002):
+        p = ig.igemm_query_plan(es, m, n, k, base, k, base, n, base, n, num_cu=256)
+        assert p["grid"] * p["threads"] < 1 << 32, p
+    for name in RING["i8" if es == 1 else "i16"]:
+        try:
+            p = ig.igemm_query_plan(es, m, n, k, num_cu=256, kernel=_kid(name))
+        except ig.IgemmError as e:
+            assert e.status == ig.IGEMM_ENOTSUP
+            continue
+        assert p["grid"] * p["threads"] < 1 << 32, p

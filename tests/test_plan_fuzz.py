@@ -44,7 +44,7 @@ def test_gemm_plan_invariants(seed):
         assert p["split"] >= 1 and p["k_chunk"] >= 1
         assert p["split"] * p["k_chunk"] >= k
         assert p["k_chunk"] <= 32768
-        assert 1 <= p["grid"] < (1 << 32) // 256
+        assert 1 <= p["grid"] and p["grid"] * p["threads"] < 1 << 32
         if not p["packed"]:
             assert p["workspace_bytes"] == 0
 
@@ -75,7 +75,7 @@ def test_conv_plan_statuses(seed):
         assert oh > 0 and ow > 0 and n > 0 and k > 0 and c > 0
         kk = r * s * c
         assert p["split"] * p["k_chunk"] >= kk and p["k_chunk"] <= 32768
-        assert 1 <= p["grid"] < (1 << 32) // 256
+        assert 1 <= p["grid"] and p["grid"] * p["threads"] < 1 << 32
         assert not p["packed"]
 
 
