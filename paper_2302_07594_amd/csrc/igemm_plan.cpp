@@ -378,6 +378,13 @@ static bool ring_dma(int es, const void *A, int64_t lda, const void *B, int64_t 
 // 128 against 94.3 with 64 x 64, 1024^3 16.4 against 11.3. int8 through registers (not
 // dma) 1000 x 3001 x 1777 20.4 with 128 x 128 against 23.7, 777 x 1111 x 2049 19.0
 // against 14.4.
+// The adds of a row go out a 64-byte request at a time, so fewer than 16 columns
+// cost as much as 16 (int16 64 x 64 tiles 100000 x 1 x 1024, s = 1 / 2 / 8 46.7 /
+// 51.4 / 103).
+// Beyond 16 slices the adds of one element, and of the elements that share its
+// line of C, also wait for each other (s = 16 / 32 / 64 / 128 / 256: int8 64 x
+// 128 tiles 64 x 64 x 262144 45.1 / 25.2 / 15.3 / 11.5 / 11.7; int16 64 x 64 tiles
+// 128 x 1 x 65536 27.9 / 19.5 / 19.4 / 27.3 / 45.0).
 static double ring_time(int id, bool dma, int64_t m, int64_t n, int64_t k, int64_t s,
                         int num_cu) {
     const KernelDesc &d = kKernels[id];
@@ -390,16 +397,24 @@ static double ring_time(int id, bool dma, int64_t m, int64_t n, int64_t k, int64
         case K_I16_RING_128x128: t = 2.0 + 0.95 * r * kt; break;
         default: t = (0.22 + 0.28 * r) * kt; break;  // K_I16_RING_64x64
     }
-    return t + (s > 1 ? 2.4e-6 * (double)m * (double)n * (double)s : 0.0);
+    if (s > 1) t += 2.4e-6 * (double)m * (double)(n < 16 ? 16 : n) * (double)s;
+    if (s > 16) t += (0.01 + 0.17 / (double)n) * (double)(s - 16);
+    return t;
 }
 
-// The slice count with the least modelled time.
+// The slice count with the least modelled time: any up to 16, then powers of two
+// (long k over few tiles).
 static int64_t ring_split(int id, bool dma, int64_t m, int64_t n, int64_t k, int num_cu) {
     const int64_t ktiles = cdiv(k, 128 / kKernels[id].es);
     int64_t best = 1;
-    for (int64_t s = 2; s <= 16 && s <= ktiles; ++s)
-        if (ring_time(id, dma, m, n, k, s, num_cu) < ring_time(id, dma, m, n, k, best, num_cu))
+    double best_t = ring_time(id, dma, m, n, k, 1, num_cu);
+    for (int64_t s = 2; s <= 512 && s <= ktiles; s += s < 16 ? 1 : s) {
+        const double t = ring_time(id, dma, m, n, k, s, num_cu);
+        if (t < best_t) {
+            best_t = t;
             best = s;
+        }
+    }
     return best;
 }
 

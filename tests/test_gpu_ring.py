@@ -198,3 +198,32 @@ def test_plans_fit_one_dispatch(es, m, n, k):
             assert e.status == ig.IGEMM_ENOTSUP
             continue
         assert p["grid"] * p["threads"] < 1 << 32, p
+
+
+def test_ring_slices_over_long_k():
+    """Long k over few tiles is sliced until the compute units are busy; tall
+    products of a few columns, whose atomic adds cost as much as 16 columns',
+    are not sliced beyond what they save."""
+    ig = _ig()
+    for es in (1, 2):
+        for m, n, k in ((64, 64, 262144), (128, 128, 262144)):
+            p = ig.igemm_query_plan(es, m, n, k, num_cu=256)
+            assert "ring" in p["kernel_name"] and p["grid"] >= 128, (es, m, n, k, p["grid"])
+            assert p["split"] * p["k_chunk"] >= k and p["k_chunk"] <= 32768
+        for m, n, k in ((100000, 1, 1024), (100000, 1, 256)):
+            p = ig.igemm_query_plan(es, m, n, k, num_cu=256)
+            assert "ring" in p["kernel_name"] and p["split"] == 1, (es, m, n, k, p["split"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["i8", "i16"])
+def test_ring_many_slices(dt):
+    """The automatic plan's slices of a long k (more than 16, the last one
+    shorter) against the oracle."""
+    m, n, k = 65, 68, 20004
+    p = _ig().igemm_query_plan(1 if dt == "i8" else 2, m, n, k, num_cu=256)
+    assert "ring" in p["kernel_name"] and p["split"] > 16
+    A, B, C = workloads.random_operands(dt, m, n, k, seed=9)
+    _, got = gpu_gemm(A, B, C, m, n, k)
+    want = oracle_gemm(A, B, C, m, n, k)
+    assert np.array_equal(got, want), describe_mismatch(got, want)
