@@ -15,9 +15,11 @@
  *   A[i,p] = A[i*lda + p]   (lda >= max(1,k))
  *   B[p,j] = B[p*ldb + j]   (ldb >= max(1,n))
  *   C[i,j] = C[i*ldc + j]   (ldc >= max(1,n))
- * Elements outside these windows are neither read nor written. A
- * column-major caller uses the identity C^T += B^T A^T: pass
- * (n, m, k, B, ldb, A, lda, C, ldc).
+ * Elements outside these windows are never written. Elements between the
+ * rows of A or B (lda > k, ldb > n), and bytes of the aligned 16 that hold the
+ * first or the last element, may be read; their values never matter. Nothing
+ * else outside the windows is read. A column-major caller uses the identity
+ * C^T += B^T A^T: pass (n, m, k, B, ldb, A, lda, C, ldc).
  *
  * Ownership and memory: A, B and C are DEVICE pointers owned by the caller
  * (allocated by any HIP allocator; the library never frees them). C itself

@@ -227,3 +227,14 @@ def test_ring_many_slices(dt):
     _, got = gpu_gemm(A, B, C, m, n, k)
     want = oracle_gemm(A, B, C, m, n, k)
     assert np.array_equal(got, want), describe_mismatch(got, want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["i8", "i16"])
+@pytest.mark.parametrize("r", range(1, 17))
+def test_ring_short_edges(dt, r):
+    """A last column tile and a last k-tile of 1 to 16 elements (their rows are
+    read in one or two pieces), and outputs and k ranges that short."""
+    for m, n, k, ld in ((70, 128 + r, 128 + r, 1), (5, r, 300, 0), (66, 130, r, 1)):
+        for name in RING[dt]:
+            _check(dt, m, n, k, name, split=1, pad=(ld, ld, 2), offsets=(1, 1, 0), seed=r)
