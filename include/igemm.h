@@ -103,7 +103,8 @@ int igemm_i8(int64_t m, int64_t n, int64_t k,
  *            32-bit atomic adds, which are exact modulo 2^32 in any order.
  *            Values above ceil(k/64) are reduced to it. Packed kernels
  *            need a workspace (the _ws calls; IGEMM_EINVAL here) and
- *            ignore split: one launch per 32768 k elements.
+ *            ignore split: one launch per 32768 k elements, sliced as the
+ *            planner sees fit (plan.grid).
  *            The int8 streaming kernel (few rows of A, B read once) rounds
  *            the k range of a slice up to 4, 8 or 16 k-tiles of 64 when
  *            the rows of A and B are whole 16-byte chunks; up to 4, 8, 16
@@ -127,7 +128,9 @@ int igemm_i8_ex(int64_t m, int64_t n, int64_t k,
 /* The launch the library would make for a call (host only, no HIP call).
  * Filled by igemm_query_plan. For packed kernels split is the number of
  * main-kernel launches (one per k chunk of k_chunk elements) and grid the
- * workgroups of each. */
+ * workgroups of each: the tiles, or, when they fill at most half of num_cu, the
+ * tiles times the slices a launch cuts its chunk into (added into C with
+ * 32-bit atomic adds; a last, shorter chunk may have fewer). */
 typedef struct igemm_plan {
     int kernel;        /* kernel index                                     */
     int elem_bytes;    /* 2 = int16 operands, 1 = int8                     */
@@ -135,7 +138,8 @@ typedef struct igemm_plan {
     int split;         /* number of k slices                               */
     int64_t k_chunk;   /* k elements per slice (multiple of bk)            */
     int64_t tiles;     /* C tiles = ceil(m/bm) * ceil(n/bn)                */
-    int64_t grid;      /* workgroups launched = tiles * split              */
+    int64_t grid;      /* workgroups launched = tiles * split (packed: see */
+                       /* above; direct: tiles, one launch per slice)      */
     int threads;       /* threads per workgroup                            */
     int vec_a, vec_b;  /* 1 if A / B rows take 16-byte vector loads (ring  */
                        /* kernels: both 1 if staged by DMA)               */

@@ -11,13 +11,12 @@
 #include "igemm_internal.h"
 
 namespace igemm {
-namespace {
 
-constexpr int kMaxDevices = 64;
+static constexpr int kMaxDevices = 64;
 
 // Compute units per device, looked up once per device. Relaxed atomics: a
 // racing first call may query twice, and both store the same value.
-std::atomic<int> g_num_cu[kMaxDevices];
+static std::atomic<int> g_num_cu[kMaxDevices];
 
 int num_cu_of_current_device() {
     int dev = 0;
@@ -34,6 +33,8 @@ int num_cu_of_current_device() {
     if (cacheable) g_num_cu[dev].store(cu, std::memory_order_relaxed);
     return cu;
 }
+
+namespace {
 
 // Scratch of igemm_i16_noalloc: one array per device, loaded with the code
 // object and kept until the process ends. In host code `scratch` names a
@@ -125,7 +126,8 @@ int packed_plan(int es, int64_t m, int64_t n, int64_t k, const void *A, int64_t 
     if (kKernels[kernel].es != es || !kKernels[kernel].packed) return IGEMM_EINVAL;
     if (workspace == nullptr || (uintptr_t)workspace % 256 != 0 || workspace_bytes < 0)
         return IGEMM_EINVAL;
-    int st = make_plan(es, m, n, k, A, lda, B, ldb, ldc, 256, kernel, -1, true, p);
+    int st = make_plan(es, m, n, k, A, lda, B, ldb, ldc, num_cu_of_current_device(), kernel, -1, true,
+                   p);
     if (st != IGEMM_OK) return st;
     return workspace_bytes < p->workspace_bytes ? IGEMM_ENOMEM : IGEMM_OK;
 }

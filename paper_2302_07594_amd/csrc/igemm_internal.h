@@ -151,6 +151,9 @@ bool small_rg_ok(int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, co
 // through registers, any alignment (0).
 bool is_ring(int id);
 
+// Compute units of the current device (256 if the runtime does not say).
+int num_cu_of_current_device();
+
 // Kernel launches for a validated plan (stream is a hipStream_t). The packed
 // launch needs a workspace of at least plan.workspace_bytes, 256-byte aligned.
 // The streaming kernel for few-row int8 products.

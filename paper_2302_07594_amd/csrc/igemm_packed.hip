@@ -1166,27 +1166,6 @@ int launch_srs_packed(const igemm_plan &p, int64_t m, int64_t n, int64_t k, int6
     return IGEMM_OK;
 }
 
-// k-tiles per slice (a multiple of four) of a multiply of `tiles` tiles, or
-// ktiles for one slice. One workgroup fits on a compute unit, so with at most
-// half as many tiles as units the rest would idle: slices up to one workgroup
-// per unit, as long as the k-tiles they save (about 0.8 us each, 0.65 int8)
-// outweigh their atomic adds into C (about 2.4 us per million). (With more than
-// half, slices in a second round, spread over the idle units, lost: 172 tiles
-// 75 us against 65.)
-static int slice_tiles(int es, int64_t m, int64_t n, int64_t tiles, int ktiles, int num_cu) {
-    int best = ktiles;
-    double best_t = (es == 2 ? 0.8 : 0.65) * ktiles;
-    for (int64_t s = 2; s * tiles <= num_cu && 4 * s <= ktiles; ++s) {
-        const int per = (int)((ktiles / 4 + s - 1) / s) * 4;
-        const double t = (es == 2 ? 0.8 : 0.65) * per + 2.4e-6 * (double)m * (double)n * (double)s;
-        if (t < best_t) {
-            best_t = t;
-            best = per;
-        }
-    }
-    return best;
-}
-
 int launch_multiply(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k, const void *A,
                     int64_t lda, int32_t *C, int64_t ldc, const void *a_part, const void *b_part,
                     void *stream_) {
@@ -1202,7 +1181,8 @@ int launch_multiply(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k
     const int tm = (int)(L.m_pad / d.bm), tn = (int)(L.n_pad / d.bn);
     const int8_t *Asrc = L.pack_a ? wa + L.off_a : (const int8_t *)A;
     const int64_t ldb_p = es * L.k_pad, lda_p = L.pack_a ? ldb_p : lda;  // bytes of a row
-    const dim3 grid((unsigned)p.grid);
+    const dim3 grid((unsigned)p.tiles);
+    const int slices = (int)(p.grid / p.tiles);  // of each launch (planner)
     if (es == 2 && L.k_pad <= 512) {
         // Short k (one chunk of four or eight k-tiles): eight waves of 64 x 32,
         // the MFMAs of the zero tiles skipped. (4096, 4096, k) one call, us,
@@ -1231,23 +1211,27 @@ int launch_multiply(int es, const igemm_plan &p, int64_t m, int64_t n, int64_t k
         const bool first = k0 == 0;
         const uint32_t *cA = first ? corrA : nullptr;
         const uint32_t kc16 = first ? 16384u * (uint32_t)k : 0u;
-        const int per = slice_tiles(es, m, n, p.tiles, ktiles, 256);
+        // k-tiles per slice: a multiple of four
+        const int per = slices == 1 ? ktiles : (ktiles / 4 + slices - 1) / slices * 4;
+        const bool sliced = per < ktiles;
         const dim3 sgrid((unsigned)(p.tiles * ((ktiles + per - 1) / per)));
-        if (ragged && per == ktiles) ktiles = kr;
-        if (per < (int)(kc / 64) && es == 2)
+        if (ragged && !sliced) ktiles = kr;
+        if (sliced && es == 2)
             igemm_packed<2, 128, 128, 64, 64, 4, 0, false, false, true><<<sgrid, 256, 0, stream>>>(
                 Asrc + 2 * k0, lda_p, Bpk + 2 * k0, ldb_p, cA, corrB, kc16, C, ldc, mi, ni,
                 ktiles, tm, tn, 0, per);
-        else if (per < (int)(kc / 64))
+        else if (sliced)
             igemm_packed<1, 256, 256, 64, 128, 4, 0, false, false, true>
                 <<<sgrid, 512, 0, stream>>>(Asrc + k0, lda_p, Bpk + k0, ldb_p, nullptr, nullptr,
                                             0u, C, ldc, mi, ni, ktiles, tm, tn, 0, per);
         else if (es == 2 && ragged)
             igemm_packed<2, 128, 128, 64, 64, 4, 0, true><<<grid, 256, 0, stream>>>(
-                Asrc + 2 * k0, lda_p, Bpk + 2 * k0, ldb_p, cA, corrB, kc16, C, ldc, mi, ni, ktiles, tm, tn, 0);
+                Asrc + 2 * k0, lda_p, Bpk + 2 * k0, ldb_p, cA, corrB, kc16, C, ldc, mi, ni,
+                ktiles, tm, tn, 0);
         else if (es == 2)
             igemm_packed<2, 128, 128, 64, 64, 4><<<grid, 256, 0, stream>>>(
-                Asrc + 2 * k0, lda_p, Bpk + 2 * k0, ldb_p, cA, corrB, kc16, C, ldc, mi, ni, ktiles, tm, tn, 0);
+                Asrc + 2 * k0, lda_p, Bpk + 2 * k0, ldb_p, cA, corrB, kc16, C, ldc, mi, ni,
+                ktiles, tm, tn, 0);
         else
             igemm_packed<1, 256, 256, 64, 128, 4><<<grid, 512, 0, stream>>>(
                 Asrc + k0, lda_p, Bpk + k0, ldb_p, nullptr, nullptr, 0u, C, ldc, mi, ni,

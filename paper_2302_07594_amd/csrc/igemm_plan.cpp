@@ -124,6 +124,31 @@ static bool packed_pays(int es, int64_t m, int64_t n, int64_t k, int num_cu) {
     return k >= 256 && m >= 1024 && n >= 1024 && tiles_of(id, m, n) >= num_cu;
 }
 
+// k slices of one launch of the packed multiply (`tiles` C tiles, ktiles k-tiles
+// of 64, a multiple of four), each of a multiple of four k-tiles, added into C
+// with atomic adds. One workgroup fits on a compute unit, so with at most half
+// as many tiles as units the rest would idle: slices up to one workgroup per
+// unit, as long as the k-tiles they save (about 0.8 us each, 0.65 int8) outweigh
+// their atomic adds (about 2.4 us per million). (With more than half, slices in a
+// second round, spread over the idle units, lost: 172 tiles 75 us against 65.)
+// int16 of at most 512 k keeps one slice (its kernel skips zero tiles instead).
+static int64_t packed_slices(int es, int64_t m, int64_t n, int64_t tiles, int64_t ktiles,
+                             int num_cu) {
+    const double tile_us = es == 2 ? 0.8 : 0.65;
+    int64_t best = ktiles;  // k-tiles per slice
+    double best_t = tile_us * (double)ktiles;
+    for (int64_t s = 2; s * tiles <= num_cu && 4 * s <= ktiles; ++s) {
+        const int64_t per = cdiv(ktiles / 4, s) * 4;
+        const double t =
+            tile_us * (double)per + 2.4e-6 * (double)m * (double)n * (double)s;
+        if (t < best_t) {
+            best_t = t;
+            best = per;
+        }
+    }
+    return es == 2 && ktiles <= 8 ? 1 : cdiv(ktiles, best);
+}
+
 // The packed kernel addresses its C tile with 32-bit byte offsets.
 static bool packed_fits(int id, int64_t ldc) {
     return (int64_t)kKernels[id].bm * ldc * 4 < INT_MAX;
@@ -644,7 +669,7 @@ int make_plan(int es, int64_t m, int64_t n, int64_t k, const void *A, int64_t ld
         out->k_chunk = L.k_pad < kMaxKChunk ? L.k_pad : kMaxKChunk;
         out->split = (int)cdiv(L.k_pad, out->k_chunk);
         out->tiles = tiles;
-        out->grid = tiles;
+        out->grid = tiles * packed_slices(es, m, n, tiles, out->k_chunk / kBK, num_cu);
         out->vec_a = (a % 16 == 0) && ((lda * es) % 16 == 0);
         out->vec_b = (b % 16 == 0) && ((ldb * es) % 16 == 0);
         out->packed = 1;

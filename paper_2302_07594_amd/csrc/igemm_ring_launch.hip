@@ -13,9 +13,10 @@ int launch(const igemm_plan &p, int64_t m, int64_t n, int64_t k, const void *A, 
            const void *B, int64_t ldb, int32_t *C, int64_t ldc, const ConvGeom *g, int epi_kind,
            int epi, void *stream) {
     const bool reg = p.vec_a == 0;
-    const void *fn = kKernels[p.kernel].es == 2 ? ring_i16(p.kernel, g != nullptr, epi_kind)
-                                                : ring_i8(p.kernel, g != nullptr, reg, epi_kind,
-                                                          p.grid <= 256);
+    const void *fn = kKernels[p.kernel].es == 2
+                         ? ring_i16(p.kernel, g != nullptr, epi_kind)
+                         : ring_i8(p.kernel, g != nullptr, reg, epi_kind,
+                                   p.grid <= num_cu_of_current_device());
     if (fn == nullptr) return IGEMM_EINVAL;
     int mi = (int)m, ni = (int)n, ki = (int)k, kc = (int)p.k_chunk;
     int tm = (int)((m + p.bm - 1) / p.bm), tn = (int)((n + p.bn - 1) / p.bn);

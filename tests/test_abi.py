@@ -677,3 +677,25 @@ def test_int8_stream_ring_plans():
                             split=2)
     assert (p["split"], p["k_chunk"], p["vec_b"]) == (2, 24 * 64, 1)
 
+
+
+def test_packed_plan_reports_its_slices():
+    """A packed multiply whose tiles fill at most half the compute units cuts
+    each launch's k chunk into slices: the plan's grid counts them, for the
+    compute units it is asked about, and is the tiles alone otherwise."""
+    names = [ig.igemm_kernel_name(i) for i in range(ig.igemm_num_kernels())]
+    for es, name in ((2, "i16_packed_128x128"), (1, "i8_packed_256x256")):
+        def plan(m, n, k, cu=256):
+            p = ig.igemm_query_plan(es, m, n, k, num_cu=cu, kernel=names.index(name))
+            assert p["grid"] % p["tiles"] == 0
+            return p["grid"] // p["tiles"], p["tiles"]
+        for m, n, k in ((64, 4096, 4096), (300, 520, 1024), (200, 300, 1300)):
+            slices, tiles = plan(m, n, k)
+            assert slices > 1 and slices * tiles <= 256
+            assert plan(m, n, k, cu=tiles)[0] == 1        # a unit per tile already
+            half = plan(m, n, k, cu=2 * tiles)[0]
+            assert 1 <= half <= 2
+        assert plan(8192, 4096, 1300)[0] == 1             # more tiles than units
+        assert plan(128, 128, 256)[0] == 1                # nothing to slice
+    # int16 up to 512 k: the zero-tile-skipping form, one slice
+    assert ig.igemm_query_plan(2, 64, 128, 512, kernel=names.index("i16_packed_128x128"))["grid"] == 1
