@@ -278,8 +278,8 @@ def bench_srs(case, kc, shift, olog, details):
     """The int16-output update (shift-round-saturate conversion per k block of
     kc, int16 C) on a workload's A and B with a random int16 C, through
     gemm_srs (the packed path on a workspace from torch's allocator where the
-    library plans it, else one fused launch per block). Algorithmic bytes: A
-    and B once and the int16 C read and written once per block."""
+    library plans it, else one launch per block on A and B in place). Algorithmic
+    bytes: A and B once and the int16 C read and written once per block."""
     import numpy as np
 
     import oracle
@@ -306,7 +306,9 @@ def bench_srs(case, kc, shift, olog, details):
     ncu = torch.cuda.get_device_properties(0).multi_processor_count
     aligned = 1 << 12   # stands for a 16-byte aligned buffer; never dereferenced
     ws = ig.igemm_srs_query(2, m, n, k, aligned, k, aligned, n, aligned, n, kc, ncu)
-    e = entry(t, ops, nbytes, 2, "packed" if ws > 0 else "fused", cycled, exact)
+    # one block of at most 2048 k is read in place, whatever workspace is asked for
+    kern = "packed" if ws > 0 and (nblocks > 1 or k > 2048) else "in place"
+    e = entry(t, ops, nbytes, 2, kern, cycled, exact)
     details.append({"name": name, "m": m, "n": n, "k": k, "kc": kc, "blocks": nblocks,
                     "workspace_bytes": ws, "sets": nsets, **e})
     return name, e

@@ -394,8 +394,8 @@ int64_t igemm_conv2d_out_dim(int64_t in, int64_t f, int64_t stride, int64_t pad,
  * (igemm_i8_srs); C is int16, m x n, row-major with leading dimension ldc,
  * updated in place; DEVICE pointers owned by the caller; any alignment.
  * shift in [0, 47] (the paper's accumulators are 48 bits wide); kc >= 0 and a
- * block of at most 32768 elements. These calls have no workspace: one fused
- * kernel launch per block, enqueued in order on `stream` (igemm_srs_ws with a
+ * block of at most 32768 elements. These calls have no workspace: one kernel
+ * launch per block, enqueued in order on `stream` (igemm_srs_ws with a
  * caller's workspace packs large int16 products first).
  *
  * Errors: IGEMM_EINVAL (before any HIP call, nothing enqueued) as for
@@ -425,15 +425,18 @@ int igemm_srs_ex(int elem_bytes, int64_t m, int64_t n, int64_t k, const void *A,
  *                    igemm_srs_ws needs for these arguments on a device with
  *                    num_cu compute units (the current device's count, as
  *                    hipDeviceAttributeMultiprocessorCount reports it), 0 when
- *                    the call takes a fused kernel (int8 operands, small
- *                    products, or blocks that are not one block or multiples
- *                    of 256). C and the pointers are only checked, never read.
+ *                    the packed path is out (int8 operands, small products, or
+ *                    blocks that are not one block or multiples of 256). One
+ *                    block of short k, or of few tiles, asks for the packed
+ *                    path's bytes too, although the call then reads A and B in
+ *                    place and leaves the workspace alone. C and the pointers
+ *                    are only checked, never read.
  *   igemm_srs_ws     workspace: device memory, 256-byte aligned
  *                    (IGEMM_EINVAL otherwise), holding the packed operands
  *                    and the per-block limb sums; at least the queried bytes
- *                    when the packed path is taken (IGEMM_ENOMEM otherwise;
- *                    nothing is enqueued). With workspace NULL the call is
- *                    igemm_srs_ex (fused kernels only). The workspace
+ *                    (IGEMM_ENOMEM otherwise; nothing is enqueued). With
+ *                    workspace NULL the call is igemm_srs_ex (A and B in
+ *                    place). The workspace
  *                    must stay untouched until the call's kernels have run;
  *                    calls that share one workspace must be ordered.
  */

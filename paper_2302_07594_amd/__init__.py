@@ -647,8 +647,8 @@ def igemm_srs_ex(elem_bytes, m, n, k, A, lda, B, ldb, C, ldc, kc=0, shift=0, rou
 
 def igemm_srs_query(elem_bytes, m, n, k, A, lda, B, ldb, C, ldc, kc=0, num_cu=0,
                     kernel=-1) -> int:
-    """Workspace bytes igemm_srs_ws needs for these arguments (0: fused
-    path). Host only. Raises IgemmError for invalid arguments."""
+    """Workspace bytes igemm_srs_ws asks for with these arguments (0: it has no
+    packed path). Host only. Raises IgemmError for invalid arguments."""
     out = ctypes.c_int64(0)
     st = int(_lib.igemm_srs_query(int(elem_bytes), m, n, k, _addr(A), lda, _addr(B), ldb,
                                   _addr(C), ldc, kc, int(num_cu), int(kernel), ctypes.byref(out)))
@@ -674,7 +674,7 @@ def gemm_srs(A, B, C, kc=0, shift=0, round_half_up=False, stream=None, kernel=-1
     shifted right by `shift` (floor, or round-half-up), saturated to int16
     and added to C modulo 2^16. `workspace` as for gemm_i16: None or 'torch'
     (a workspace from torch's allocator when the packed path is taken, so the
-    call may be captured into a graph), 'none' (fused kernels only) or a
+    call may be captured into a graph), 'none' (A and B in place) or a
     uint8 tensor. Returns C."""
     if stream is None and workspace is None:
         st = (_native or _load_native()).srs(A, B, C, kc, shift, round_half_up, kernel)

@@ -216,8 +216,9 @@ int run_conv(int es, const igemm_conv2d_desc *d, const void *X, const void *W, i
 }
 
 // int16-output update: the packed path for large int16 products whose blocks
-// fall on the packed k-tiles (one block, or blocks of a multiple of 256, at
-// most 64), else one fused launch per k block of kc elements, in order. All
+// fall on the packed k-tiles (one long block, or blocks of a multiple of 256, at
+// most 64), else one launch per k block of kc elements on the operands in
+// place (ring kernel or fused tiles), in order. All
 // blocks are planned before the first launch, so an error enqueues nothing.
 int srs_check(int es, int64_t m, int64_t n, int64_t k, const void *A, int64_t lda, const void *B,
               int64_t ldb, const void *C, int64_t ldc, int64_t kc, int shift, int round_half_up,
@@ -282,8 +283,9 @@ int run_srs(int es, int64_t m, int64_t n, int64_t k, const void *A, int64_t lda,
         // One block of short k, or at most one packed tile per compute unit:
         // the ring kernel on the operands in place (the loop below) instead of
         // the two pack passes and the packed multiply (us, ring / packed: m = n
-        // = 4096 with k = 290 47 / 63, 1024 85 / 103, 2048 145 / 163, 4096 267
-        // / 262; 2048 x 2048 x 4096 73 / 84).
+        // = 4096 with k = 290 44 / 60, 1024 85 / 103, 2048 145 / 163, 4096 267
+        // / 262; 2048 x 2048 x 4096 73 / 84). The query still asks for the packed
+        // workspace, and a smaller one stays refused.
         igemm_plan rp;
         const bool in_place =
             pp.packed && kernel < 0 && nblocks == 1 &&
