@@ -4,11 +4,13 @@
 ``csrc/*.hip`` and ``csrc/*.cpp`` with hipcc into
 ``paper_2302_07594_amd/libigemm.so``. The library exports the C ABI declared
 in ``include/igemm.h``. ``binding/igemm_torch.cpp``, the tensor calls' native
-path, is compiled with g++ against torch's headers and that library into
-``paper_2302_07594_amd/_igemm_torch.so``.
+path, is compiled against torch's headers and that library into
+``paper_2302_07594_amd/_igemm_torch.so`` (left out where torch is not
+installed: the C library needs neither torch nor Python).
 
 Next to the library, ``libigemm.so.sha256`` records the SHA-256 of every
-source, header and compiler flag the library was built from
+source, header and compiler flag the library and the binding were built from
+and of the torch and Python versions the binding was built for
 (``source_hash()``); ``is_current()`` compares it with the tree, so that
 tests can rebuild a library that is out of date instead of running it.
 """
@@ -17,6 +19,7 @@ from __future__ import annotations
 import concurrent.futures
 import glob
 import hashlib
+import importlib.metadata
 import importlib.util
 import os
 import shutil
@@ -73,9 +76,27 @@ def _hash_files(paths, flags) -> str:
     return h.hexdigest()
 
 
+def torch_version():
+    """Version of the installed torch, or None without one."""
+    if importlib.util.find_spec("torch") is None:
+        return None
+    try:
+        return importlib.metadata.version("torch")
+    except importlib.metadata.PackageNotFoundError:  # a source tree
+        return "unknown"
+
+
+# Compiler flags of the binding (its include and library folders apart).
+BINDING_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1",
+                 "-DUSE_ROCM"]
+
+
 def source_hash(extra_flags=None) -> str:
-    """SHA-256 over every source and header of the library and the flags."""
-    return _hash_files(sources() + headers() + [BINDING_SRC], compile_flags(extra_flags))
+    """SHA-256 over every source and header of the library and the binding, the
+    flags and the versions the binding is built for."""
+    return _hash_files(sources() + headers() + [BINDING_SRC],
+                       compile_flags(extra_flags) + BINDING_FLAGS +
+                       [f"torch {torch_version()}", f"python {sysconfig.get_python_version()}"])
 
 
 # Everything the packed multiply kernel is built from (its source and the
@@ -113,7 +134,8 @@ def is_current() -> bool:
             stamp = f.read().strip()
     except OSError:
         return False
-    return os.path.exists(LIB) and os.path.exists(BINDING) and stamp == source_hash()
+    built = os.path.exists(LIB) and (os.path.exists(BINDING) or torch_version() is None)
+    return built and stamp == source_hash()
 
 
 def _run(cmd, verbose):
@@ -129,15 +151,23 @@ def _run(cmd, verbose):
 
 
 def _build_binding(verbose: bool) -> None:
-    """Compile binding/igemm_torch.cpp against torch and the built library."""
-    torch_dir = list(importlib.util.find_spec("torch").submodule_search_locations)[0]
+    """Compile binding/igemm_torch.cpp against torch and the built library, with
+    g++, or hipcc's host compiler where there is none. Without torch there is
+    nothing to bind to (and no tensor to call with)."""
+    spec = importlib.util.find_spec("torch")
+    if spec is None:
+        if verbose:
+            print("torch is not installed: the library is built without the tensor binding",
+                  flush=True)
+        return
+    torch_dir = list(spec.submodule_search_locations)[0]
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     inc = [INCLUDE, os.path.join(torch_dir, "include"),
            os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
            os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    cxx = ["g++"] if shutil.which("g++") else [hipcc(), "-x", "c++"]
     tmp = BINDING + ".tmp"
-    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1",
-          "-DUSE_ROCM"] + [f for d in inc for f in ("-I", d)] +
+    _run(cxx + BINDING_FLAGS + [f for d in inc for f in ("-I", d)] +
          [BINDING_SRC, "-o", tmp, "-L", os.path.join(torch_dir, "lib"), "-ltorch_python",
           "-ltorch_hip", "-ltorch_cpu", "-lc10_hip", "-lc10", "-L", HERE,
           "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN"], verbose)

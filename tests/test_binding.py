@@ -139,3 +139,32 @@ def test_native_path_streams_workspaces_and_transforms():
     assert torch.equal(ig.gemm_packed_b(Ad, pb, C0.clone()), want)
     with pytest.raises(Exception):
         torch.func.vmap(lambda a: ig.gemm_i16(a, Bd, C0.clone()))(Ad[None])
+
+
+def test_library_builds_without_torch(monkeypatch, tmp_path):
+    """The C library needs no torch: without it (or without its headers) the
+    binding is left out instead of failing a build whose library is done, and
+    a binding counts as current only for the torch it was built against."""
+    from paper_2302_07594_amd import build
+    lib, binding, stamp = (tmp_path / n for n in ("lib.so", "binding.so", "stamp"))
+    monkeypatch.setattr(build, "LIB", str(lib))
+    monkeypatch.setattr(build, "BINDING", str(binding))
+    monkeypatch.setattr(build, "STAMP", str(stamp))
+    lib.write_bytes(b"")
+    binding.write_bytes(b"")
+    stamp.write_text(build.source_hash() + "\n")
+    assert build.is_current()
+    monkeypatch.setattr(build, "torch_version", lambda: "0.0.1")   # another torch
+    assert not build.is_current()
+    monkeypatch.undo()
+    monkeypatch.setattr(build, "LIB", str(lib))
+    monkeypatch.setattr(build, "BINDING", str(binding))
+    monkeypatch.setattr(build, "STAMP", str(stamp))
+    binding.unlink()
+    assert not build.is_current()
+    monkeypatch.setattr(build.importlib.util, "find_spec", lambda name: None)
+    assert not build.is_current()                  # built for a torch that is gone
+    build._build_binding(False)                    # nothing to build, no error
+    assert not binding.exists()
+    stamp.write_text(build.source_hash() + "\n")
+    assert build.is_current()
