@@ -103,38 +103,70 @@ def test_native_and_python_paths_agree():
 
 
 @pytest.mark.gpu
-def test_native_path_streams_workspaces_and_transforms():
-    """The current stream is the one a call runs on; a packed product takes its
-    workspace from the allocator, eagerly and under capture; a batched tensor
-    is not taken for a plain one."""
+@pytest.mark.parametrize("op", ["gemm", "srs"])
+def test_native_path_streams_and_workspaces(op):
+    """The current stream is the one a call runs on, and a product that packs
+    takes its workspace from the allocator, on that stream, eagerly and under
+    capture: memory that later work on the stream overwrites must not be in
+    use still."""
     import torch
     ig = _ig()
-    m = n = 1100
-    k = 2000
+    m, n, k = 2048, 2048, 1536
     A, B, C = workloads.random_operands("i16", m, n, k, seed=8)
     Ad, Bd = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
-    C0 = torch.from_numpy(C).cuda()
-    want = ig.gemm_i16(Ad, Bd, C0.clone(), workspace="torch")
+    ncu = torch.cuda.get_device_properties(0).multi_processor_count
+    if op == "gemm":
+        need = ig.igemm_query_plan(2, m, n, k, Ad, k, Bd, n, None, n, ncu)["workspace_bytes"]
+        C0, call = torch.from_numpy(C).cuda(), ig.gemm_i16
+    else:
+        C0 = torch.from_numpy(C.astype(np.int16)).cuda()
+        need = ig.igemm_srs_query(2, m, n, k, Ad, k, Bd, n, C0, n, 512, ncu)
+
+        def call(a, b, c, **kw):
+            return ig.gemm_srs(a, b, c, kc=512, shift=9, round_half_up=True, **kw)
+    assert need > 0
+    native = ig._load_native()
+    c = C0.clone()
+    assert (native.gemm(2, Ad, Bd, c, -1, -1) if op == "gemm" else
+            native.srs(Ad, Bd, c, 512, 9, True, -1)) == ig.IGEMM_OK   # not left to Python
+    want = call(Ad, Bd, C0.clone(), workspace="torch")
+    assert torch.equal(c, want)
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):
         c = C0.clone()
         for _ in range(3):
-            ig.gemm_i16(Ad, Bd, c)
+            call(Ad, Bd, c)
+            torch.full((need // 4 + 4096,), -1, dtype=torch.int32, device="cuda")
     side.synchronize()
     thrice = C0.clone()
     for _ in range(3):
-        ig.gemm_i16(Ad, Bd, thrice, workspace="torch")
+        call(Ad, Bd, thrice, workspace="torch")
     assert torch.equal(c, thrice)
     c = C0.clone()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
-        ig.gemm_i16(Ad, Bd, c)
+        call(Ad, Bd, c)
+        torch.full((need // 4 + 4096,), -1, dtype=torch.int32, device="cuda")
     for _ in range(3):
         c.copy_(C0)
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(c, want)
+        assert torch.equal(call(Ad, Bd, C0.clone()), want)   # eager work between replays
+
+
+@pytest.mark.gpu
+def test_native_path_packed_b_and_transforms():
+    """gemm_packed_b gives what the one-call product gives; a batched tensor is
+    not taken for a plain one."""
+    import torch
+    ig = _ig()
+    m, n, k = 1100, 1100, 2000
+    A, B, C = workloads.random_operands("i16", m, n, k, seed=8)
+    Ad, Bd = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    C0 = torch.from_numpy(C).cuda()
+    want = ig.gemm_i16(Ad, Bd, C0.clone(), workspace="torch")
     pb = ig.pack_b(Bd)
     assert torch.equal(ig.gemm_packed_b(Ad, pb, C0.clone()), want)
     with pytest.raises(Exception):

@@ -115,9 +115,8 @@ def test_packed_int8_extremes_multi_chunk(value):
 
 # k counts whose k-tiles of 64 are not a multiple of four. int16 with k up to
 # 512 skips the MFMAs of the zero tiles (eight-wave kernel: k = 1, 130, 290,
-# 330, 420); beyond it, it multiplies only the tiles that hold data when the
-# padding spans three of them (1300: 21 tiles, through the tail chosen at run
-# time) and the zero padding up to a multiple of four otherwise (1345).
+# 330, 420); beyond it, few tiles like these are cut into k slices of whole
+# fours (1300, 1345). The unsliced forms have a test of their own below.
 RAGGED_K = [1, 130, 290, 330, 420, 1300, 1345]
 
 
@@ -126,6 +125,54 @@ def test_packed_int16_ragged_k_tiles(k):
     m, n = 200, 300
     A, B, C = workloads.random_operands("i16", m, n, k, seed=800 + k)
     _check("i16", A, B, C, m, n, k)
+
+
+# More than half as many tiles as compute units: one slice. int16 beyond k = 512
+# multiplies only the k-tiles that hold data when the padding spans three of
+# them (1088 and 1300: 17 and 21 tiles, the tail chosen at run time), the zero
+# padding up to a multiple of four otherwise (1345); int8 with A packed (1000)
+# and read in place (768).
+UNSLICED = [("i16", 1100, 2000, 1088), ("i16", 2048, 2048, 1300), ("i16", 1100, 2000, 1345),
+            ("i8", 2900, 2900, 1000), ("i8", 4096, 2304, 768)]
+
+
+@pytest.mark.parametrize("case", UNSLICED, ids=lambda c: "-".join(map(str, c)))
+def test_packed_unsliced(case):
+    ig = _ig()
+    dt, m, n, k = case
+    p = ig.igemm_query_plan(2 if dt == "i16" else 1, m, n, k, kernel=_kid(dt), num_cu=256)
+    assert p["grid"] == p["tiles"] > 128
+    A, B, C = workloads.random_operands(dt, m, n, k, seed=810 + k)
+    _check(dt, A, B, C, m, n, k)
+
+
+@pytest.mark.parametrize("value", [-32768, 32767])
+@pytest.mark.parametrize("k", [1088, 32768 + 577])
+def test_packed_int16_unsliced_extremes(value, k):
+    """Every limb sum at its bound through the tail chosen at run time, alone
+    and after a whole first chunk."""
+    m, n = 1450, 1500
+    p = _ig().igemm_query_plan(2, m, n, k, kernel=_kid("i16"), num_cu=256)
+    assert p["grid"] == p["tiles"] > 128 and p["split"] == (1 if k < 32768 else 2)
+    A = np.full((m, k), value, np.int16)
+    B = np.full((k, n), value, np.int16)
+    C = np.zeros((m, n), np.int32)
+    _, got = gpu_gemm(A, B, C, m, n, k, kernel=_kid("i16"))
+    assert np.all(got == np.int64(value * value * k).astype(np.int32))
+
+
+@pytest.mark.parametrize("dt,m,n,k", [("i16", 640, 640, 2304), ("i16", 500, 900, 2304),
+                                      ("i8", 700, 700, 2304), ("i8", 768, 700, 2304),
+                                      ("i16", 640, 640, 32768 + 2304)])
+def test_packed_slices_with_a_short_last_one(dt, m, n, k):
+    ig = _ig()
+    p = ig.igemm_query_plan(2 if dt == "i16" else 1, m, n, k, kernel=_kid(dt), num_cu=256)
+    slices = p["grid"] // p["tiles"]
+    ktiles = -(-min(k, 32768) // 256) * 4   # of the first launch, in fours
+    per = -(-(ktiles // 4) // slices) * 4
+    assert slices > 1 and ktiles % per != 0, (slices, ktiles, per)
+    A, B, C = workloads.random_operands(dt, m, n, k, seed=820 + m)
+    _check(dt, A, B, C, m, n, k)
 
 
 @pytest.mark.parametrize("value", [-32768, 32767])
@@ -285,9 +332,8 @@ def test_wrapper_workspace_on_side_stream(kind):
     del junk
 
 
-# Short k over many tiles: k-tile counts 1 to 9 around the boundaries (the
-# ragged tail variants and the zero padding up to a multiple of four tiles),
-# ragged m and n.
+# Short k over several tiles: k-tile counts 1 to 9 around the boundaries (up to
+# 512 the zero tiles' MFMAs skipped; 513: k slices), ragged m and n.
 SHORT_K = [2, 63, 64, 65, 128, 200, 256, 290, 383, 448, 511, 512, 513]
 
 

@@ -3,6 +3,10 @@ and convolutions) against the CPU oracle, bit for bit: edges of its tiles and
 k-tiles, every row alignment (DMA and register staging), k slices that end
 inside a k-tile, the conversion at shifts around its two forms, and the shapes
 where the automatic plans take it."""
+import os
+import shutil
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -76,8 +80,50 @@ def test_ring_extreme_values(dt):
                 assert np.array_equal(got, want), (name, k, a, b)
 
 
-# 32 and more of the small tiles: the automatic int16-output plan is the ring
-# kernel (asserted by the plan rule's test below for the same sizes).
+# Every int16-output form of the kernel that the automatic plan takes (the calls
+# name no ring kernel): operand type, m, n, k and padding of A, B and C -> tile
+# shape and staging (1: DMA, 0: registers), asserted by test_ring_srs_plans. The
+# last two int8 ones have one workgroup per unit at most and more.
+SRS_FORMS = {
+    ("i8", 451, 532, 300, (0, 0, 3)): ("i8_ring_64x128", 1),
+    ("i8", 451, 530, 300, (1, 0, 3)): ("i8_ring_64x128", 0),
+    ("i16", 451, 530, 300, (1, 0, 3)): ("i16_ring_64x64", 0),
+    ("i8", 4000, 2044, 644, (0, 0, 1)): ("i8_ring_128x128", 1),
+    ("i8", 2000, 2001, 901, (0, 0, 2)): ("i8_ring_128x128", 0),
+    ("i8", 4001, 2047, 385, (0, 0, 0)): ("i8_ring_128x128", 0),
+    ("i16", 2000, 2040, 333, (0, 1, 2)): ("i16_ring_128x128", 0),
+}
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host C++ compiler")
+def test_ring_srs_plans(tmp_path):
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    csrc = os.path.join(root, "paper_2302_07594_amd", "csrc")
+    exe = str(tmp_path / "srs_plan")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(root, "include"), "-I", csrc,
+                    os.path.join(csrc, "igemm_plan.cpp"),
+                    os.path.join(root, "tests", "srs_plan_driver.cpp"), "-o", exe], check=True)
+    for (dt, m, n, k, pad), (name, vec) in SRS_FORMS.items():
+        args = (1 if dt == "i8" else 2, m, n, k, k + pad[0], n + pad[1])
+        out = subprocess.run([exe] + [str(x) for x in args], check=True, capture_output=True,
+                             text=True).stdout.split()
+        assert out[:2] == [name, str(vec)], (args, out)
+        if m in (2000, 4001) and dt == "i8":
+            assert (int(out[2]) <= 256) == (m == 2000)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("form", SRS_FORMS, ids=lambda f: "-".join(map(str, f[:4])))
+def test_ring_srs_forms(form):
+    """Ragged in every extent, both sides of each conversion form."""
+    from test_gpu_srs import _operands
+    dt, m, n, k, pad = form
+    A, B, C = _operands(dt, m, n, k, seed=m + k, pad=pad)
+    for shift, rnd in ((0, False), (9, True), (16, True), (17, False), (31, True)):
+        got = check_srs(A, B, C, m, n, k, 0, shift, rnd)
+        assert np.array_equal(got[:, n:], C[:, n:])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dt", ["i8", "i16"])
 @pytest.mark.parametrize("conv", [(0, 0, False), (0, 1, True), (0, 15, True), (0, 16, False),
@@ -121,6 +167,26 @@ def test_ring_conv(dt, case):
     check_conv(dt, n, h, w, c, k, r, s, stride, pad, dil, seed=n + c)
     # weights at an odd dword: register staging
     check_conv(dt, n, h, w, c, k, r, s, stride, pad, dil, seed=n + k, w_off=1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", ["i8", "i16"])
+@pytest.mark.parametrize("w_off", [0, 1])
+@pytest.mark.parametrize("big", [True, False])
+def test_ring_conv_forms(dt, w_off, big):
+    """Each tile shape and staging (int8 weights at odd bytes, and int16: through
+    registers), whole k and in slices (a deep window alone asks for them)."""
+    ig = _ig()
+    n, h, c, k = (32, 28, 64, 200) if big else (1, 8, 4112, 256)
+    es = 1 if dt == "i8" else 2
+    d = ig.conv_desc(n, h, h, c, k, 3, 3, (1, 1), (1, 1), (1, 1))
+    want = (RING[dt][0 if big else 1], 1 if dt == "i8" and w_off == 0 else 0)
+    for split in (-1, 2):
+        p = ig.igemm_conv2d_query_plan(es, d, W=0x10000 + es * w_off, num_cu=256, split=split)
+        assert (p["kernel_name"], p["vec_a"]) == want
+        assert p["split"] == (2 if split == 2 else 1) or (not big and p["split"] > 16)
+        check_conv(dt, n, h, h, c, k, 3, 3, (1, 1), (1, 1), (1, 1), seed=n + w_off, split=split,
+                   w_off=w_off)
 
 
 def test_ring_plan_rules():

@@ -160,19 +160,20 @@ def test_block_beyond_limit_is_refused():
     assert st == _ig().IGEMM_ENOTSUP and np.array_equal(got, C)
 
 
-@pytest.mark.parametrize("path", ["packed", "fused"])
+@pytest.mark.parametrize("path", ["auto", "packed", "fused"])
 def test_paper_shape_full(path):
     """The paper's GEMM shape (4096, 4096, 290) with its k_c = 290 and shift
     0, full-range int16 operands and a random int16 C (the configuration the
-    benchmark times): every element against the oracle, on the packed path
-    (with a workspace, as the benchmark runs it) and on the fused path (no
-    workspace)."""
+    benchmark times): every element against the oracle, as the benchmark runs
+    it (automatic plan: the ring kernel in place), on the packed path (named)
+    and on the fused tiles (named, no workspace)."""
     case = workloads.WORKLOADS["i16_paper"].cases[0]
     m, n, k = case.m, case.n, case.k
     A, B, _ = workloads.generate(case)
     C = np.random.default_rng(case.seed).integers(-32768, 32767, size=(m, n), dtype=np.int16,
                                                   endpoint=True)
-    _, got = _gpu(A, B, C, m, n, k, 290, 0, False, workspace=path == "packed")
+    kernel = {"auto": -1, "packed": _kid("i16_packed_128x128"), "fused": _kid("i16_64x64")}[path]
+    _, got = _gpu(A, B, C, m, n, k, 290, 0, False, kernel=kernel, workspace=path != "fused")
     want = _oracle(A, B, C, m, n, k, 290, 0, False)
     assert np.array_equal(got, want), _describe(got, want)
 
