@@ -98,15 +98,21 @@ __device__ __forceinline__ v4i load_u16(const char *p) {
 // tiny: the whole matrix has fewer than 16 bytes (uniform).
 __device__ __forceinline__ v4i load_edge(const char *base, int off, int end, bool tiny) {
     if (!tiny) {
-        const int o = min(off, end - 16), sh = 8 * min(off - o, 16);
+        const int o = min(off, end - 16), b = off - o;  // b bytes to drop, >= 0
         const v4i v = load_u16(base + o);
-        const uint64_t x = (uint64_t)(u32)v.y << 32 | (u32)v.x;
-        const uint64_t y = (uint64_t)(u32)v.w << 32 | (u32)v.z;
-        // (y << 1 << (63 - s): 0 for s = 0)
-        const uint64_t l = sh < 64 ? x >> (sh & 63) | y << 1 << (63 - (sh & 63))
-                                   : (sh < 128 ? y >> (sh & 63) : 0);
-        const uint64_t h = sh < 64 ? y >> (sh & 63) : 0;
-        return v4i{(int)(u32)l, (int)(u32)(l >> 32), (int)(u32)h, (int)(u32)(h >> 32)};
+        const u32 w0 = (u32)v.x, w1 = (u32)v.y, w2 = (u32)v.z, w3 = (u32)v.w;
+        // Whole words, then bytes, in 32 bits: a 64-bit shift whose amount is
+        // in the last register a kernel has allocated takes v0 instead (measured
+        // on gfx950: rows shifted by their lane's number of bits), and the
+        // compiler keeps it out of that register on gfx90a only.
+        const bool s1 = (b & 4) != 0, s2 = (b & 8) != 0, s4 = b >= 16;
+        const u32 t0 = s1 ? w1 : w0, t1 = s1 ? w2 : w1, t2 = s1 ? w3 : w2, t3 = s1 ? 0u : w3;
+        const u32 u0 = s4 ? 0u : (s2 ? t2 : t0), u1 = s4 ? 0u : (s2 ? t3 : t1);
+        const u32 u2 = s4 || s2 ? 0u : t2, u3 = s4 || s2 ? 0u : t3;
+        return v4i{(int)__builtin_amdgcn_alignbyte(u1, u0, (u32)b),
+                   (int)__builtin_amdgcn_alignbyte(u2, u1, (u32)b),
+                   (int)__builtin_amdgcn_alignbyte(u3, u2, (u32)b),
+                   (int)__builtin_amdgcn_alignbyte(0u, u3, (u32)b)};
     }
     u32 w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll 1
@@ -362,25 +368,45 @@ igemm_ring(const char *__restrict__ A, int64_t lda, const char *__restrict__ B, 
             const int k0 = kt * BK, left = klen - k0;  // k positions left, >= 1
             const char *ak = a_base + (int64_t)kt * RA;
             const char *bk = b_base + (int64_t)k0 * ldb_b;
-            // (ends of the matrices, from here; offsets in the windows are below it)
+            // Ends of the matrices, from here (offsets in the windows are below
+            // 2^31). A tile inside both takes plain loads, all in flight at once;
+            // the others, in the last row or column of tiles, bounded ones.
             const int a_end = (int)min(((int64_t)(m - 1 - m0) * lda + (k - kbeg - k0)) * ES,
                                        (int64_t)0x7fffffff);
             const int b_end = (int)min(((int64_t)(k - 1 - kbeg - k0) * ldb + (n - n0)) * ES,
                                        (int64_t)0x7fffffff);
+            int a_off[DPA], b_off[DPB];
 #pragma unroll
-            for (int d = 0; d < DPA; ++d) {
-                if constexpr (AM == 1)
-                    va[d] = __builtin_amdgcn_raw_buffer_load_b128(Xrs, conv_off(d, kt), 0, 0);
-                else
-                    va[d] = load_edge(ak, min(a_row[d], mrows - 1) * lda_b + 16 * a_lc[d], a_end,
-                                      a_tiny);
+            for (int d = 0; d < DPA; ++d)
+                a_off[d] = min(a_row[d], mrows - 1) * lda_b + 16 * a_lc[d];
+#pragma unroll
+            for (int d = 0; d < DPB; ++d)
+                b_off[d] = min(b_row[d], left - 1) * ldb_b + 16 * b_lc[d];
+            if ((AM == 1 || (mrows - 1) * lda_b + RA <= a_end) &&
+                (left - 1) * ldb_b + RB <= b_end) {
+#pragma unroll
+                for (int d = 0; d < DPA; ++d) {
+                    if constexpr (AM == 1)
+                        va[d] = __builtin_amdgcn_raw_buffer_load_b128(Xrs, conv_off(d, kt), 0, 0);
+                    else
+                        va[d] = load_u16(ak + a_off[d]);
+                }
+#pragma unroll
+                for (int d = 0; d < DPB; ++d) vb[d] = load_u16(bk + b_off[d]);
+            } else {
+#pragma unroll
+                for (int d = 0; d < DPA; ++d) {
+                    if constexpr (AM == 1)
+                        va[d] = __builtin_amdgcn_raw_buffer_load_b128(Xrs, conv_off(d, kt), 0, 0);
+                    else
+                        va[d] = load_edge(ak, a_off[d], a_end, a_tiny);
+                }
+#pragma unroll
+                for (int d = 0; d < DPB; ++d) vb[d] = load_edge(bk, b_off[d], b_end, b_tiny);
             }
 #pragma unroll
-            for (int d = 0; d < DPB; ++d) {
-                const v4i v = load_edge(bk, min(b_row[d], left - 1) * ldb_b + 16 * b_lc[d], b_end,
-                                        b_tiny);
-                vb[d] = b_row[d] < left ? v : v4i{0, 0, 0, 0};
-            }
+            for (int d = 0; d < DPB; ++d)
+                if (b_row[d] >= left) vb[d] = v4i{0, 0, 0, 0};
         }
     };
     // int16 is split here, once per element: a chunk's 8 elements become 8

@@ -304,3 +304,23 @@ def test_ring_short_edges(dt, r):
     for m, n, k, ld in ((70, 128 + r, 128 + r, 1), (5, r, 300, 0), (66, 130, r, 1)):
         for name in RING[dt]:
             _check(dt, m, n, k, name, split=1, pad=(ld, ld, 2), offsets=(1, 1, 0), seed=r)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("k,kc", [(374, 290), (84, 0), (128, 0), (200, 0)])
+def test_ring_edge_tiles_row_by_row(k, kc):
+    """Every k row of the edge tiles (rows at odd addresses, more workgroups than
+    units): with A one at p alone, the int16 output is row p of B."""
+    import torch
+    ig = _ig()
+    m, n = 2420, 965
+    rng = np.random.default_rng(k)
+    B = torch.from_numpy(rng.integers(-128, 128, size=(k, 967), dtype=np.int8)).cuda()[:, 2:]
+    A = torch.zeros(m, k + 5, dtype=torch.int8, device="cuda")
+    C = torch.zeros(m, n, dtype=torch.int16, device="cuda")
+    for p in range(k):
+        A.zero_()
+        A[:, 1 + p] = 1
+        C.zero_()
+        ig.gemm_srs(A[:, 1:1 + k], B, C, kc=kc)
+        assert torch.equal(C, B[p].to(torch.int16).expand(m, n)), p
