@@ -282,9 +282,9 @@ int run_srs(int es, int64_t m, int64_t n, int64_t k, const void *A, int64_t lda,
         if (pp.packed && workspace_bytes < need) return IGEMM_ENOMEM;
         // One block of short k, or at most one packed tile per compute unit:
         // the ring kernel on the operands in place (the loop below) instead of
-        // the two pack passes and the packed multiply (us, ring / packed: m = n
-        // = 4096 with k = 290 44 / 60, 1024 85 / 103, 2048 145 / 163, 4096 267
-        // / 262; 2048 x 2048 x 4096 73 / 84). The query still asks for the packed
+        // the two pack passes and the packed multiply (us, operands in the
+        // caches, ring / packed: m = n = 4096 with k = 290 41 / 62, 1024 71 / 96,
+        // 2048 134 / 142, 4096 235 / 236; 2048 x 2048 x 4096 62 / 72). The query still asks for the packed
         // workspace, and a smaller one stays refused.
         igemm_plan rp;
         const bool in_place =

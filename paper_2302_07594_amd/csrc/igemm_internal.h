@@ -53,13 +53,14 @@ extern const KernelDesc kKernels[K_COUNT];
 
 // Workspace of the packed path, in two parts (byte offsets from 256-byte
 // aligned bases), so that B can be packed once and reused:
-//   A part (a_bytes): es planes of m_pad rows (int16: high limb, then offset
-//     low limb), absent for int8 A that is already aligned and tile-shaped,
-//     then m_pad row corrections (int16);
-//   B part (b_bytes): es planes of n_pad rows (the columns of B), then n_pad
-//     column corrections (int16; pack_b adds each k slice's column sums).
-// Planes are k-contiguous int8 rows of k_pad bytes, zero beyond k. The
-// one-call workspace is the A part followed by the B part.
+//   A part (a_bytes): m_pad rows, absent for int8 A that is already aligned
+//     and tile-shaped, then m_pad row corrections (int16);
+//   B part (b_bytes): n_pad rows (the columns of B), then n_pad column
+//     corrections (int16; pack_b adds each k slice's column sums).
+// Rows are k-contiguous, es * k_pad bytes, zero beyond k: int8 elements, or for
+// int16, per 64 elements, their 64 high limbs and then their 64 offset low limbs
+// (one 128-byte line). The one-call workspace is the A part followed by the B
+// part.
 struct PackedLayout {
     int64_t m_pad, n_pad, k_pad;
     int64_t kspan;     // k rows per pack_b workgroup

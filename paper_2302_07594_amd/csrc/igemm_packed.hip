@@ -5,13 +5,14 @@
 // around the micro-kernel; Sec. 5.1 pre-packs A_c once for DL inference). On
 // the GPU this is done for the whole operands, once per call, by two small
 // memory-bound kernels:
-//   * pack A: int16 rows are split into a high and an offset-low int8 limb
-//     plane (k-contiguous, zero-padded to m_pad x k_pad) and the row limb sums
-//     are reduced into one 32-bit correction per row; int8 A is only copied
-//     when its rows are not 16-byte aligned or not tile multiples;
-//   * pack B: B is transposed to k-contiguous columns (and split into limb
-//     planes for int16), zero-padded to n_pad x k_pad, with per-column limb
-//     sums reduced per k slice.
+//   * pack A: int16 rows are split into high and offset-low int8 limbs (per 64
+//     elements a 128-byte line, 64 high limbs and then 64 low ones; zero-padded
+//     to m_pad x k_pad elements) and the row limb sums are reduced into one
+//     32-bit correction per row; int8 A is only copied when its rows are not
+//     16-byte aligned or not tile multiples;
+//   * pack B: B is transposed to k-contiguous columns (split into the same
+//     lines for int16), zero-padded to n_pad x k_pad, with per-column limb sums
+//     reduced per k slice.
 // The main kernel then reads both operands with global-to-LDS DMA loads
 // (global_load_lds_dwordx4: no VGPRs, no staging instructions) into a
 // four-stage LDS ring, three k-tiles ahead of the matrix cores, and runs the
@@ -54,7 +55,7 @@ __global__ void __launch_bounds__(256) clear_u32(uint32_t *__restrict__ p, int n
 // limbs, then their 64 offset low limbs) and corrA[i] = 32768*sum(h) + 128*sum(l) mod 2^32,
 // and, if corrB is given, zeroes corrB[0, n_pad).
 // For the int16-output update (bsA given): also the exact per-block limb
-// sums of the row, block b = [b bspan, (b + 1) bspan) of the planes (bspan a
+// sums of the row, block b = elements [b bspan, (b + 1) bspan) (bspan a
 // multiple of 256, at most 64 blocks), at bsA[2 (b m_pad + i)] (high limbs)
 // and + 1 (offset low limbs), m_pad = gridDim.x; and zeroes clr[0, nclr)
 // (B's block sums, which pack_b adds into).
@@ -205,7 +206,7 @@ pack_a_i8(const int8_t *__restrict__ A, int64_t lda, int m, int k, int k_pad,
 // Workgroup (blockIdx.x, blockIdx.y) covers columns [64x, 64x + 64) and the
 // k slice [kspan*y, kspan*(y+1)). Per pass, thread (rg, cc) loads 4 rows x 16
 // bytes, transposes 4x4 byte blocks in registers (and for int16 separates the
-// limb planes), parks the per-column dwords in LDS, and the workgroup writes
+// limbs), parks the per-column dwords in LDS, and the workgroup writes
 // each column's k run out contiguously. For int16 the per-column limb sums of
 // the slice are added into corrB[col] (zeroed by pack_a_i16, which runs first),
 // and, for the int16-output update (bsB given), the exact per-block limb sums
@@ -215,7 +216,8 @@ pack_a_i8(const int8_t *__restrict__ A, int64_t lda, int m, int k, int k_pad,
 template <int ES, bool VEC>
 __global__ void __launch_bounds__(256)
 pack_b(const void *__restrict__ Bv, int64_t ldb, int k, int n, int k_pad, int kspan, int n_pad,
-       int8_t *__restrict__ Bpk, uint32_t *__restrict__ corrB, uint32_t *__restrict__ bsB = nullptr, int bspan = 0) {
+       int8_t *__restrict__ Bpk, uint32_t *__restrict__ corrB,
+       uint32_t *__restrict__ bsB = nullptr, int bspan = 0) {
     constexpr int P = ES;                 // output planes
     constexpr int CC = ES == 2 ? 8 : 4;   // 16-byte column chunks per workgroup (64 columns)
     constexpr int RG = 256 / CC;          // row groups of 4 rows
@@ -484,7 +486,7 @@ igemm_packed(const int8_t *__restrict__ Ap, int64_t lda_p,
     // an operand whose r0 has the same place in the swizzle's period of 16
     // rows: all of them (int8, 16 rows per block), or the even and the odd
     // ones (int16, 8 rows; the odd ones' chunks differ in bit 2). The planner
-    // keeps 16 rows of a plane below 2^32 bytes.
+    // keeps 16 k_pad (or, int8 A in place, 16 lda) bytes below 2^32.
     constexpr int CPR = RB / 16;
     auto rswz = [](int row) -> int { return P == 2 ? (row >> 1) & 7 : swz(row); };
     const u32 lrow = (u32)(lane / CPR);
@@ -670,7 +672,7 @@ igemm_packed(const int8_t *__restrict__ Ap, int64_t lda_p,
     read_frags(ic<0>{}, ic<0>{}, ic<0>{});
     // Groups of NST steps in which every step starts a DMA and prefetches,
     // then the remaining T = ktiles - kt steps (T in [NST-1, 2*NST-2];
-    // ktiles >= NST - 1, a multiple of four unless RAGGED). The planes are
+    // ktiles >= NST - 1, a multiple of four unless RAGGED). The rows are
     // zero-padded to a multiple of four k-tiles, so the prologue's loads stay
     // inside them.
     // EPI 2-5: this lane's running int16 sums, two per register (16-bit lanes
@@ -1099,7 +1101,7 @@ int launch_srs_packed(const igemm_plan &p, int64_t m, int64_t n, int64_t k, int6
     const int8_t *wa = (const int8_t *)a_part, *wb = (const int8_t *)b_part;
     const int8_t *Apk = wa + L.off_a, *Bpk = wb + L.off_b;
     const int64_t ld = 2 * L.k_pad;  // bytes of a packed row
-    const int kb = nblocks == 1 ? (int)L.k_pad : (int)kc;  // block span in the planes
+    const int kb = nblocks == 1 ? (int)L.k_pad : (int)kc;  // elements of a block
     // the block sums, written by the pack kernels
     uint32_t *sa = sums, *sb = sums + 2 * nblocks * L.m_pad;
     const KernelDesc &d = kKernels[p.kernel];
@@ -1134,7 +1136,7 @@ int launch_srs_packed(const igemm_plan &p, int64_t m, int64_t n, int64_t k, int6
         return hipGetLastError() == hipSuccess ? IGEMM_OK : IGEMM_EHIP;
     }
     // Otherwise one launch per block, in order (the update modulo 2^16 makes
-    // the order immaterial); block q spans [q kb, q kb + kb) of the planes.
+    // the order immaterial); block q spans elements [q kb, q kb + kb).
     for (int64_t q = 0; q < nblocks; ++q) {
         const int64_t k0 = q * kb;
         const int64_t span = L.k_pad - k0 < kb ? L.k_pad - k0 : kb;   // a multiple of 256

@@ -394,18 +394,18 @@ static bool ring_dma(int es, const void *A, int64_t lda, const void *B, int64_t 
 // fitted to its measured times on 256 compute units: `r` workgroups per unit
 // share it, each k-tile (128 int8, 64 int16) costs the unit a fixed part and
 // one per workgroup, and slices pay for their atomic adds into C, about 2.4 us
-// per million. Measured (us, s = 1 / 2 / 4): int8 64 x 128 tiles 64 x 4096 x
-// 4096 21.1 / 14.0 / 9.6, 256 x 4096 x 4096 21.1 / 16.2 / 20.2, 1024^3 6.5 /
-// 8.7 / 13.1; int16 64 x 64 tiles 64 x 4096 x 4096 39.1 / 23.0 / 15.2, 1024^3
-// 11.3 / 11.7 / 16.7, 128 x 128 tiles 512 x 4096 x 4096 55.0 / 43.3 / 54.4.
-// Tile shapes: int8 2048 x 4096 x 4096 50.0 with 128 x 128 against 64.5 with
-// 64 x 128, 1536^3 17.0 against 13.9; int16 1024 x 4096 x 4096 74.8 with 128 x
-// 128 against 94.3 with 64 x 64, 1024^3 16.4 against 11.3. int8 through registers (not
-// dma) 1000 x 3001 x 1777 20.4 with 128 x 128 against 23.7, 777 x 1111 x 2049 19.0
-// against 14.4.
+// per million. The fit is to operands that are not cached; with operands in the
+// caches (us, s = 1 / 2 / 4): int8 64 x 128 tiles 64 x 4096 x 4096 13.1 / 9.4 /
+// 7.5, 256 x 4096 x 4096 14.1 / 12.8 / 15.9, 1024^3 6.1 / 8.6 / 12.8; int16 64 x 64
+// tiles 64 x 4096 x 4096 30.8 / 17.8 / 12.4, 1024^3 9.8 / 11.2 / 15.9, 128 x 128
+// tiles 512 x 4096 x 4096 49.6 / 39.5 / 50.6. Tile shapes: int8 2048 x 4096 x 4096
+// 42.3 with 128 x 128 against 55.1 with 64 x 128, 1536^3 11.7 against 10.2; int16
+// 1024 x 4096 x 4096 61.4 with 128 x 128 against 85.2 with 64 x 64, 1024^3 13.6
+// against 9.8. int8 through registers (not dma) 1000 x 3001 x 1777 18.3 with 128 x
+// 128 against 21.4, 777 x 1111 x 2049 15.9 against 13.0.
 // The adds of a row go out a 64-byte request at a time, so fewer than 16 columns
 // cost as much as 16 (int16 64 x 64 tiles 100000 x 1 x 1024, s = 1 / 2 / 8 46.7 /
-// 51.4 / 103).
+// 51.4 / 103 when eight were taken; 45.2 / 48.3 now).
 // Beyond 16 slices the adds of one element, and of the elements that share its
 // line of C, also wait for each other (s = 16 / 32 / 64 / 128 / 256: int8 64 x
 // 128 tiles 64 x 64 x 262144 45.1 / 25.2 / 15.3 / 11.5 / 11.7; int16 64 x 64 tiles
@@ -526,13 +526,14 @@ static int auto_kernel(int es, int64_t m, int64_t n, int64_t k, const void *A, i
         (small_ok(m, n, k, A, lda, B, ldb, ldc) || small_rg_ok(m, n, k, A, lda, B, ldb, ldc)))
         return K_I16_SMALL_64x64;
     // The ring kernel takes what is left above the few-row shapes. int8: by DMA
-    // (rows at 4-byte addresses) anything over 32 rows (64^3 3.0 us against 9.0
-    // on 128x128 tiles, 512 x 4096 x 4096 22.9 against 34.7, 2048 x 4096 x 4096
-    // 50.0 against 89.3); through registers from 32 tiles (777 x 1111 x 2049
-    // 16.2 against 23.2; below, its bounds-checked last k-tile costs more than
-    // it gains: 146 x 501 x 801 9.5 against 7.3). int16: more than one k-tile
-    // and 32 tiles, or fewer over a long k (1536^3 25.9 against 45.8 us, 201 x
-    // 201 x 6001 10.3 against 17.9, 146 x 97 x 792 5.9 against 5.1).
+    // (rows at 4-byte addresses) anything over 32 rows (us, operands in the
+    // caches: 64^3 3.2 against 9.0 on 128x128 tiles, 512 x 4096 x 4096 17.8 against
+    // 30.0, 2048 x 4096 x 4096 44.1 against 82.6); through registers from 32 tiles
+    // (777 x 1111 x 2049 13.6 against 21.3; with fewer the fused tiles' many short
+    // slices won, 146 x 501 x 801 7.3 against 9.5 when it was measured). int16:
+    // more than one k-tile and 32 tiles, or fewer over a long k (1536^3 24.0
+    // against 45.2 us, 201 x 201 x 6001 7.9 against 17.0, 146 x 97 x 792 5.9
+    // against 5.1 when it was measured).
     igemm_plan rp{};
     if (m > 32) {
         const int rid =
@@ -543,6 +544,10 @@ static int auto_kernel(int es, int64_t m, int64_t n, int64_t k, const void *A, i
                 return rid;
         }
     }
+    // (Below, the tiles for more than 32 rows are reached by few int8 tiles at odd
+    // addresses, few int16 tiles or a single k-tile, and by leading dimensions or
+    // sizes beyond the ring kernel's 32-bit windows or one dispatch; the last are
+    // all that is left for K_I8_256x256 and K_I16_128x128.)
     if (es == 1) {
         StreamShape ss;
         if (m <= 32 && n >= 512 && k >= 256 && (uintptr_t)B % 8 == 0 && ldb % 8 == 0 &&
@@ -656,7 +661,7 @@ int make_plan(int es, int64_t m, int64_t n, int64_t k, const void *A, int64_t ld
         // kMaxKChunk elements; the launches add into C in stream order.
         PackedLayout L;
         packed_layout(es, m, n, k, id, A, lda, &L);
-        // The multiply kernel addresses 16 rows of a plane with 32-bit lane
+        // The multiply kernel addresses 16 rows of bytes (8 of int16) with 32-bit lane
         // offsets.
         const int64_t plane_ld = L.pack_a ? L.k_pad : (L.k_pad > lda ? L.k_pad : lda);
         if (tiles > kMaxGrid || L.m_pad > kMaxGrid || L.n_pad / 64 > kMaxGrid ||
@@ -814,7 +819,7 @@ int make_srs_plan(int es, int64_t m, int64_t n, int64_t kb, const void *A, int64
     *out = igemm_plan{};
     int id = kernel;
     // The ring kernel from 32 of its small tiles on (int8 1024 x 4096 x 1024
-    // 10.5 us against 23.5 on 32x256 tiles), blocks of at most 2^14 elements
+    // 9.0 us against 24.7 on 32x256 tiles), blocks of at most 2^14 elements
     // (its int16 conversion's bound).
     if (id < 0 && m > 32 && kb <= (1 << 14) &&
         tiles_of(es == 2 ? K_I16_RING_64x64 : K_I8_RING_64x128, m, n) >= 32 &&

@@ -13,7 +13,7 @@
 //     (ds_read_b64_tr_b8) on the way to the matrix cores, not by byte permutes
 //     on the way in (the fused tiles' way). A's rows in a k-tile are 128 bytes
 //     (BK = 128 int8, 64 int16): one request a row, where 64-byte rows took two
-//     (int8 2048 x 4096 x 4096 54 us against 62);
+//     (int8 2048 x 4096 x 4096 54 us against 62 when it was chosen);
 //   * int8 operands whose rows start at 4-byte addresses (REG = false) go by
 //     buffer DMA (buffer_load_dwordx4 ... lds). Rows beyond m, and rows of B
 //     beyond the k range, lie outside the resources and land as zeros, so no
@@ -24,13 +24,14 @@
 //     wave, cost the same matrix work twice the vector instructions: (4096,
 //     4096, 1024) 90 us against 105), and the LDS writes of tile kt + 1 are
 //     issued between the matrix instructions of tile kt. Only k-tiles that
-//     touch the end of a matrix take bounds-checked loads;
+//     reach beyond the k range or a matrix's end are apart: they go first, and
+//     take bounded loads where they touch the end;
 //   * AM = 1: A is the IM2ROW matrix of a convolution (Sec. 4.2) whose
 //     channel rows are whole 16-byte chunks, each chunk inside one filter tap.
 // Two or more workgroups share a compute unit (one, int16 128 x 128). Against
-// the fused tiles that took these products (us): int8 512 x 4096 x 4096 22.9
-// from 34.7, 1000 x 3001 x 1777 28.3 from 51.4; int16 777 x 1111 x 2049 22.0
-// from 32.0, 1536^3 25.9 from 45.8.
+// the fused tiles that took these products (us a call, operands in the caches):
+// int8 512 x 4096 x 4096 17.8 from 30.0, 1000 x 3001 x 1777 19.1 from 44.6; int16
+// 777 x 1111 x 2049 21.8 from 30.6, 1536^3 24.0 from 45.2.
 //
 // int16 exactness (limb identity): with h = x >> 8, l' = (x & 255) - 128,
 //   sum_p x_p y_p = 65536 S_hh + 256 (S_hl' + S_l'h) + S_l'l'
@@ -467,7 +468,8 @@ igemm_ring(const char *__restrict__ A, int64_t lda, const char *__restrict__ B, 
 #pragma unroll
                 for (int r = 0; r < M::REGS; ++r) acc[a][i][j][r] = 0;
     // int16: limb sums of this wave's share, its rows of A or its columns of
-    // B, so that each row and column is summed by one wave.
+    // B: each row by one wave, each column by one or, with four waves across a
+    // tile, two (to the same value).
     constexpr int NPS = ES == 2 ? (TM > TN ? TM : TN) : 1;
     int sum_h[NPS], sum_l[NPS];
 #pragma unroll
@@ -648,9 +650,10 @@ igemm_ring(const char *__restrict__ A, int64_t lda, const char *__restrict__ B, 
     // row, and of a column, are formed once, where the sum is, and read from
     // LDS: the conversion was almost half of the kernel's vector instructions,
     // which bound it (rocprofv3: 12.1 million, 40 % of the cycles, against 17 %
-    // for the matrix cores); with both, (4096, 4096, 290) 45.8 us to 43.5,
-    // (4065, 670, 1213) in blocks of 290 53.7 to 52.4. int8: v fits in 30 bits; shifts above 31 act as 31, and the
-    // rounding unit of 31 already rounds every v to 0.
+    // for the matrix cores); with both, and operands that are not cached, (4096,
+    // 4096, 290) 45.8 us to 43.5, (4065, 670, 1213) in blocks of 290 53.7 to 52.4.
+    // int8: v fits in 30 bits; shifts above 31 act as 31, and the rounding unit
+    // of 31 already rounds every v to 0.
     const int shift = epi & 0xff;
     const bool round = ((epi >> 8) & 1) != 0 && shift > 0;
     auto update = [&](auto mode_c) __attribute__((always_inline)) {

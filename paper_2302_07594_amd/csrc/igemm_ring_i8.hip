@@ -8,12 +8,13 @@ using namespace ring;
 // workgroups per compute unit. By DMA four waves: 128 x 128 tiles in 64 x 64, two
 // 32 KB stages, 64 x 128 tiles in 32 x 64, three 24 KB stages. Through registers
 // eight waves of half the columns and two stages: they read more from LDS but
-// cover each other's waits for loads and stores (777 x 1111 x 2049 14.4 us
-// against 16.5, 1000 x 3001 x 1777 20.4 against 23.1; by DMA 1024 x 4096 x 4096
-// 36.3 against 35.2). Through registers 128 x 128 tiles need more than the 128
-// registers of two workgroups: a grid of one workgroup per unit at most takes
-// them (ROCC 1; 1000 x 3001 x 1777 25.8 us against 28.4, operands not cached), a
-// larger one spills a few (2048 x 4096 x 4096 53.5 against 57.3).
+// cover each other's waits for loads and stores (when chosen, operands in the
+// caches: 777 x 1111 x 2049 14.4 us against 16.5, 1000 x 3001 x 1777 20.4 against
+// 23.1; by DMA 1024 x 4096 x 4096 36.3 against 35.2). Through registers 128 x 128
+// tiles need more than the 128 registers of two workgroups: a grid of one
+// workgroup per unit at most takes them (ROCC 1; 1000 x 3001 x 1777 25.8 us
+// against 28.4, operands not cached), a larger one spills two to six (2048 x 4096
+// x 4096 53.5 against 57.3).
 template <int BM, int BN, int WM, int WN, int NST, int ROCC>
 static const void *pick_i8(bool conv, bool reg, int epi) {
 #define IGEMM_R(am, rg, ep)                                                                  \
