@@ -238,7 +238,10 @@ int igemm_i16_noalloc(int64_t m, int64_t n, int64_t k,
  *            misaligned, IGEMM_ENOMEM if too small; nothing is enqueued).
  * Both calls are asynchronous on `stream`; the multiply must be ordered
  * after the pack (same stream, or an event) and the workspace kept intact
- * between them. Sizes beyond the packed path's limits return IGEMM_ENOTSUP.
+ * between them. The packed layout belongs to one version of the library
+ * (igemm_version): a buffer that was saved is packed again after an update, not
+ * handed to the new library (version 300 and earlier kept int16 limbs in two
+ * planes). Sizes beyond the packed path's limits return IGEMM_ENOTSUP.
  */
 int igemm_pack_i16(int64_t m, int64_t n, int64_t k,
                    const int16_t *A, int64_t lda,
@@ -279,7 +282,8 @@ int igemm_i8_prepacked(int64_t m, int64_t n, int64_t k,
  *            aligned, at least plan.packed_b_bytes (IGEMM_EINVAL for NULL or
  *            misaligned, IGEMM_ENOMEM if too small; nothing is enqueued).
  * Asynchronous on `stream`; a multiply must be ordered after the pack and
- * `packed_b` kept intact between them. Multiplies that share one packed B
+ * `packed_b` kept intact between them (and, like the workspace above, within one
+ * version of the library). Multiplies that share one packed B
  * may run concurrently (they only read it). Sizes beyond the packed path's
  * limits return IGEMM_ENOTSUP.
  */

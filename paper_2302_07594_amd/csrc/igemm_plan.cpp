@@ -1003,7 +1003,7 @@ const char *igemm_strerror(int status) {
     }
 }
 
-int igemm_version(void) { return 300; }
+int igemm_version(void) { return 400; }  // 400: int16 limbs in one packed row
 
 int64_t igemm_conv2d_out_dim(int64_t in, int64_t f, int64_t stride, int64_t pad, int64_t dil) {
     return igemm::conv_out_dim(in, f, stride, pad, dil);

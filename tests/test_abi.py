@@ -699,3 +699,9 @@ def test_packed_plan_reports_its_slices():
         assert plan(128, 128, 256)[0] == 1                # nothing to slice
     # int16 up to 512 k: the zero-tile-skipping form, one slice
     assert ig.igemm_query_plan(2, 64, 128, 512, kernel=names.index("i16_packed_128x128"))["grid"] == 1
+
+
+def test_version_counts_the_packed_layout():
+    """Packed buffers belong to one library version; int16 limbs share a row
+    since 400."""
+    assert ig.igemm_version() >= 400
