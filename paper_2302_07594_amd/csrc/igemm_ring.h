@@ -95,7 +95,7 @@ __device__ __forceinline__ v4i load_u16(const char *p) {
 // several chunks are in flight together; it runs past the end of a row into the
 // next one, whose values end up in columns or against rows that the caller
 // discards. (Bounded by the row's end instead, rows of fewer than 16 bytes went
-// a byte at a time, 2.4 us a k-tile: int8 10000 x 8 x 256 7.8 us, now 5.0.)
+// a byte at a time, 2.4 us a k-tile: int8 10000 x 8 x 256 7.9 us, now 5.3.)
 // tiny: the whole matrix has fewer than 16 bytes (uniform).
 __device__ __forceinline__ v4i load_edge(const char *base, int off, int end, bool tiny) {
     if (!tiny) {
